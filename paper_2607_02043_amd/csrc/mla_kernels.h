@@ -57,7 +57,7 @@ struct AttnArgs {
     int32_t dec_total_tiles;
     int32_t grid;              // persistent workgroups of the attention launch
     int32_t dec_first_wgs;     // workgroups 0 .. dec_first_wgs - 1 take decode items before chunk items
-    int32_t merge_hsplit;      // merge workgroups per split decode row (1, 4 or 8: heads split among them)
+    int32_t merge_hsplit;      // size class of the most split decode row: 1 (at most 4 parts), 4 (at most 16) or 8
     int32_t out_bf16;
     int32_t spin_limit;        // sleeps of a bounded wait before it gives up (kSpinLimit)
     ChunkRoute route;          // chunk requests it sends to the multi-head path are left out of this launch

@@ -423,66 +423,122 @@ __device__ __forceinline__ void store_out4(const AttnArgs &a, int row, int head,
 }
 
 // ------------------------------------------------------------------ merge
-// Merge the key-split partials of one output row in split order.  Split s
-// holds an unnormalised output o_s (16 heads x 512 dims) with its max m_s
-// and sum l_s in log2 units; slot(s) gives pointers to both.  256 threads:
-// head tid / 16, dims (tid % 16) * 32 .. + 32.  The loads of up to four splits
-// go out together; the running result is rescaled whenever the max grows.
+// Merge the key-split partials of output rows.  Split s holds an
+// unnormalised output o_s (16 heads x 512 dims) with its max m_s and sum l_s
+// in log2 units; slot(s) gives pointers to both.  A wavefront takes one head
+// and every SW-th split of it, lane l holding dims 4 l .. + 3 and 256 + 4 l ..;
+// the SW wavefronts of a head meet in LDS, in a fixed order.
+//
+// Bound by latency: the partials are small (0.1 .. 35 MB a call) and were just
+// written by other XCDs, so every load is a round trip past the L2 and what
+// counts is how many such rounds follow one another.  All loads of a batch
+// of splits go out together, and rows cut into many parts spread over
+// more wavefronts, so a row takes one or two rounds.  (One thread loop per head
+// and row before, a block-wide scan of the lengths in front: 18.2 us for 4 rows
+// of 75 parts, now 8.3; 16.5 -> 12.2 us for 128 rows of up to 23 parts; 20.9 ->
+// 12.1 us for 1069 chunk rows and 37 decode rows.  More workgroups per
+// row of few parts cost more in launches than they overlap: 256 rows of
+// 2 to 4 parts take 10.5 us with 4 workgroups a row, 15.6 with 8.)
 struct SplitRef {
     const float *o, *ml;
 };
 
-template <int NH, typename Slot>
-__device__ void merge_heads(const AttnArgs &a, int row, int hh0, int nsplit, Slot slot) {
-    // NH heads per workgroup: head hh0 + tid / (256 / NH), DPT value dims per thread
-    constexpr int TPH = kThreads / NH, DPT = kDv / TPH, NV = DPT / 4;
-    constexpr int B = NH >= 16 ? 2 : NH >= 4 ? 8 : 16;  // splits whose loads go out together
-    const int tid = threadIdx.x;
-    const int hh = hh0 + tid / TPH, d0 = (tid % TPH) * DPT;
-    float M = kNegInf, den = 0.f;
-    f32x4 o[NV];
-#pragma unroll
-    for (int k = 0; k < NV; ++k) o[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < nsplit; s0 += B) {
+// o, M, den += splits s0, s0 + SW, .. of head hh (B of them in flight).
+template <int B, int SW, typename Slot>
+__device__ __forceinline__ void merge_splits(int s0, int nsplit, int hh, int lane, Slot slot, f32x4 (&o)[2], float &M,
+                                             float &den) {
+    for (; s0 < nsplit; s0 += B * SW) {
         float ms[B], ls[B];
-        f32x4 v[B][NV];
+        f32x4 v[B][2];
 #pragma unroll
         for (int q = 0; q < B; ++q) {
             ms[q] = kNegInf;
             ls[q] = 0.f;
-            if (s0 + q < nsplit) {
-                const SplitRef sr = slot(s0 + q);
+            v[q][0] = v[q][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (s0 + q * SW < nsplit) {
+                const SplitRef sr = slot(s0 + q * SW);
                 ms[q] = sr.ml[hh * 2];
                 ls[q] = sr.ml[hh * 2 + 1];
-                const f32x4 *src = reinterpret_cast<const f32x4 *>(sr.o + hh * kDv + d0);
-#pragma unroll
-                for (int k = 0; k < NV; ++k) v[q][k] = src[k];
-            } else {
-#pragma unroll
-                for (int k = 0; k < NV; ++k) v[q][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+                const f32x4 *src = reinterpret_cast<const f32x4 *>(sr.o + hh * kDv) + lane;
+                v[q][0] = src[0];
+                v[q][1] = src[64];
             }
         }
+        float m_new = M;
+#pragma unroll
+        for (int q = 0; q < B; ++q) m_new = fmaxf(m_new, ms[q]);
+        const float c_old = (M == kNegInf) ? 0.f : exp2f(M - m_new);
+        den *= c_old;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) o[k] = o[k] * c_old;
 #pragma unroll
         for (int q = 0; q < B; ++q) {
             if (ms[q] == kNegInf) continue;  // a split that saw no key of this row
-            const float m_new = fmaxf(M, ms[q]);
-            const float c_old = (M == kNegInf) ? 0.f : exp2f(M - m_new);
-            const float c_new = exp2f(ms[q] - m_new);
-            den = den * c_old + ls[q] * c_new;
+            const float c = exp2f(ms[q] - m_new);
+            den += ls[q] * c;
 #pragma unroll
-            for (int k = 0; k < NV; ++k) o[k] = o[k] * c_old + v[q][k] * c_new;
+            for (int k = 0; k < 2; ++k) o[k] = o[k] + v[q][k] * c;
+        }
+        M = m_new;
+    }
+}
+
+__device__ __forceinline__ void store_merged(const AttnArgs &a, int row, int hh, int lane, const f32x4 (&o)[2], float M,
+                                             float den) {
+    const float inv = 1.f / den;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) store_out4(a, row, hh, 4 * lane + 256 * k, o[k] * inv);
+    if (a.lse && lane == 0) a.lse[(size_t)row * kHeads + hh] = (M + log2f(den)) * kLn2;
+}
+
+// Heads hh0 .. hh0 + 4 / SW - 1 of a row with many splits; s_o holds 4 x 512 floats, s_ml 4 x 2.
+template <int B, int SW, typename Slot>
+__device__ void merge_heads(const AttnArgs &a, int row, int hh0, int nsplit, Slot slot, float *s_o, float *s_ml) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int hh = hh0 + wv / SW, part = wv % SW;
+    f32x4 o[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    float M = kNegInf, den = 0.f;
+    merge_splits<B, SW>(part, nsplit, hh, lane, slot, o, M, den);
+    if constexpr (SW > 1) {
+        if (part != 0) {
+            f32x4 *dst = reinterpret_cast<f32x4 *>(s_o + wv * kDv) + lane;
+            dst[0] = o[0];
+            dst[64] = o[1];
+            if (lane == 0) {
+                s_ml[2 * wv] = M;
+                s_ml[2 * wv + 1] = den;
+            }
+        }
+        __syncthreads();
+        if (part != 0) return;
+#pragma unroll
+        for (int w = 1; w < SW; ++w) {
+            const float m = s_ml[2 * (wv + w)], l = s_ml[2 * (wv + w) + 1];
+            if (m == kNegInf) continue;  // fewer splits than wavefronts
+            const float m_new = fmaxf(M, m);
+            const float c_old = (M == kNegInf) ? 0.f : exp2f(M - m_new), c = exp2f(m - m_new);
+            const f32x4 *src = reinterpret_cast<const f32x4 *>(s_o + (wv + w) * kDv) + lane;
+            den = den * c_old + l * c;
+            o[0] = o[0] * c_old + src[0] * c;
+            o[1] = o[1] * c_old + src[64] * c;
             M = m_new;
         }
     }
-    const float inv = 1.f / den;
-#pragma unroll
-    for (int k = 0; k < NV; ++k) store_out4(a, row, hh, d0 + 4 * k, o[k] * inv);
-    if (a.lse && tid % TPH == 0) a.lse[(size_t)row * kHeads + hh] = (M + log2f(den)) * kLn2;
+    store_merged(a, row, hh, lane, o, M, den);
 }
 
+// A whole row, four heads per wavefront.
 template <typename Slot>
 __device__ void merge_row(const AttnArgs &a, int row, int nsplit, Slot slot) {
-    merge_heads<kHeads>(a, row, 0, nsplit, slot);
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < kHeads / 4; ++k) {
+        const int hh = wv * (kHeads / 4) + k;
+        f32x4 o[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+        float M = kNegInf, den = 0.f;
+        merge_splits<2, 1>(0, nsplit, hh, lane, slot, o, M, den);
+        store_merged(a, row, hh, lane, o, M, den);
+    }
 }
 
 // ------------------------------------------------------------ decode path
@@ -877,27 +933,32 @@ __device__ void decode_wg(const AttnArgs &a, int w, char *smem, int *s_tmp, int 
     TRACE(4);
 }
 
-// Merge kernel side: workgroup (r, part) merges heads part * 16 / hsplit ..
-// of decode request r when its tiles span several decode units.  Unit v
+// Merge workgroups of a split decode row: 4, 8 or 16, of 4, 2 or 1 heads
+// each, for rows of at most 4, at most 16 or more parts (merge_hsplit 1, 4, 8).
+__host__ __device__ __forceinline__ int merge_wgs(const AttnArgs &a) {
+    return a.merge_hsplit == 8 ? 16 : 4;
+}
+
+// Merge kernel side: workgroup `part` of decode request r merges its share of
+// the heads when the request's tiles span several decode units.  Unit v
 // keeps its first segment in slot 2 v and its last one in slot 2 v + 1.
-__device__ void decode_merge(const AttnArgs &a, int r, int part, int *s_tmp) {
+template <bool MANY>
+__device__ void decode_merge(const AttnArgs &a, int r, int part, float *s_o, float *s_ml) {
     if (a.ws_dec_o == nullptr || r >= a.num_reqs) return;
-    const int tid = threadIdx.x;
-    // T = decode tiles of the requests before r (one block-wide sum per 256 requests)
+    const int lane = threadIdx.x & 63;
+    const int row = a.cu_q[r], p = a.prefix[r], next = a.cu_q[r + 1];
+    // T = decode tiles of the requests before r; every wavefront sums them by
+    // itself (their lengths are one round of loads for up to 256 requests)
     int T = 0;
-    for (int base = 0; base < r; base += blockDim.x) {
-        const int q = base + tid;
-        int nt = 0;
-        if (q < r) {
-            const int row0 = a.cu_q[q], p = a.prefix[q];
-            nt = (p >= 0 && row0 >= 0 && row0 < a.num_rows) ? dec_tiles(p, a.cu_q[q + 1] - row0) : 0;
-        }
-        int total;
-        block_scan_excl(nt, s_tmp, total);
-        T += total;
+#pragma unroll 4
+    for (int q = lane; q < r; q += 64) {
+        const int row0 = a.cu_q[q], pq = a.prefix[q];
+        T += (pq >= 0 && row0 >= 0 && row0 < a.num_rows) ? dec_tiles(pq, a.cu_q[q + 1] - row0) : 0;
     }
-    const int row = a.cu_q[r], p = a.prefix[r];
-    if (p < 0 || row < 0 || row >= a.num_rows || a.cu_q[r + 1] - row != 1) return;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) T += __shfl_xor(T, d, 64);
+    T = __builtin_amdgcn_readfirstlane(T);
+    if (p < 0 || row < 0 || row >= a.num_rows || next - row != 1) return;
     const int S = a.dec_unit_tiles, nt = dec_tiles(p, 1);
     const int w0 = T / S, w1 = (T + nt - 1) / S;
     if (w0 == w1) return;  // one unit wrote the row itself
@@ -907,12 +968,10 @@ __device__ void decode_merge(const AttnArgs &a, int r, int part, int *s_tmp) {
         return SplitRef{a.ws_dec_o + sl * kHeads * kDv, a.ws_dec_ml + sl * kHeads * 2};
     };
     const int n = w1 - w0 + 1;
-    if (a.merge_hsplit == 8)
-        merge_heads<2>(a, row, 2 * part, n, slot);
-    else if (a.merge_hsplit == 4)
-        merge_heads<4>(a, row, 4 * part, n, slot);
+    if constexpr (MANY)
+        merge_heads<8, 4>(a, row, part, n, slot, s_o, s_ml);
     else
-        merge_heads<16>(a, row, 0, n, slot);
+        merge_heads<4, 1>(a, row, 4 * part, n, slot, s_o, s_ml);
 }
 
 // ------------------------------------------------------------- chunk path
@@ -1377,18 +1436,21 @@ __global__ __launch_bounds__(kAttnThreads, 1) void attention_kernel(AttnArgs a) 
 
 // Merge workgroups of split decode rows (none when no decode row was split).
 __host__ __device__ __forceinline__ int merge_dec_wgs(const AttnArgs &a) {
-    return a.ws_dec_o != nullptr ? a.num_reqs * a.merge_hsplit : 0;
+    return a.ws_dec_o != nullptr ? a.num_reqs * merge_wgs(a) : 0;
 }
 
 // Split merges, after the attention kernel (the kernel boundary makes every
-// partial visible): first merge_hsplit workgroups per request (decode rows
-// split across units), then one per (chunk item, block row).
-__global__ __launch_bounds__(kThreads) void combine_kernel(AttnArgs a) {
+// partial visible): first merge_wgs workgroups per request (decode rows split
+// across units), then one per (chunk item, block row).
+template <bool MANY>
+__global__ __launch_bounds__(kThreads, MANY ? 4 : 5) void combine_kernel(AttnArgs a) {
     __shared__ int s_tmp[16];
+    __shared__ __attribute__((aligned(16))) float s_o[4 * kDv];
+    __shared__ float s_ml[8];
     const int b = blockIdx.x;
     const int n_dec = merge_dec_wgs(a);
     if (b < n_dec) {
-        decode_merge(a, b / a.merge_hsplit, b % a.merge_hsplit, s_tmp);
+        decode_merge<MANY>(a, b / merge_wgs(a), b % merge_wgs(a), s_o, s_ml);
         return;
     }
     // one workgroup per (chunk item, row of its block): the item with key split
@@ -1546,7 +1608,10 @@ hipError_t launch_combine(const AttnArgs &a, hipStream_t s) {
     if (grid_ll > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const int grid = (int)grid_ll;
     if (grid == 0) return hipSuccess;
-    hipLaunchKernelGGL(combine_kernel, dim3(grid), dim3(kThreads), 0, s, a);
+    if (a.merge_hsplit == 8)
+        hipLaunchKernelGGL(combine_kernel<true>, dim3(grid), dim3(kThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL(combine_kernel<false>, dim3(grid), dim3(kThreads), 0, s, a);
     return hipGetLastError();
 }
 
