@@ -1,6 +1,7 @@
-"""Merge of key-split rows at the sizes where its code branches: rows cut into
-as many parts as one, two or more load rounds take, on either side of the limit
-that picks another split of the heads over workgroups.
+"""Merge of key-split rows and the append, at the sizes where their code
+branches: rows cut into as many parts as one, two or more load rounds take, on
+either side of the limits that pick another split of the heads over workgroups;
+batches around the 64 requests whose lengths one load round covers.
 """
 import numpy as np
 import pytest
@@ -47,3 +48,15 @@ def test_chunk_rows_of_one_to_five_parts(chunk):
     _, out_ref, lse_ref = oracle.step(wl.batch, li, W.SOFTMAX_SCALE)
     assert_close(g.out_np(), out_ref, g.lse_np(), lse_ref, what=wl.name)
 
+
+@pytest.mark.parametrize("reqs", [1, 63, 64, 65, 130])
+def test_append_of_many_requests(reqs):
+    rng = np.random.default_rng(reqs)
+    prefix, rows = rng.integers(0, 50, reqs), rng.integers(1, 4, reqs)
+    log(f"[gpu] append, {reqs} requests")
+    wl = W.custom(prefix, rows, page_size=8, seed=reqs, name=f"{reqs} requests")
+    li = wl.layer(0)
+    g = run_layer(wl.batch, li)
+    pool_ref, out_ref, lse_ref = oracle.step(wl.batch, li, W.SOFTMAX_SCALE)
+    assert np.array_equal(g.pool_np(), pool_ref), "append: pool differs from the oracle"
+    assert_close(g.out_np(), out_ref, g.lse_np(), lse_ref, what=wl.name)
