@@ -85,15 +85,21 @@ int cu_count() {
 // 64 x 128 (3), 64 x 64 (4), 32 x 64 (6) that still gives at least 0.85
 // workgroups per CU (fewer leaves CUs idle; more is a second round of
 // workgroups for large tiles), and the register-staged 256 x 128 tile for the
-// narrow batched value up-projection once it has 1024 rows.  fp32 activations
+// narrow batched value up-projection once it has 1024 rows.  Up to 48 rows
+// (not gathered) take the few-row kernel: before / after attention 17.1 / 14.9 us
+// tiled against 13.0 / 10.9 at 19 rows, 17.3 / 14.8 against 16.3 / 13.2 at 48;
+// at 64 rows it loses, 17.8 / 15.1 against 20.8 / 15.9.  fp32 activations
 // use 64-column tiles.  MLA_GEMM_BM / MLA_GEMM_BN / MLA_GEMM_D override the
 // choice (for tuning; a shape that is not instantiated fails the launch).
-proj::GemmShape pick_shape(long long M, int N, int batch, int epi, bool a_f32) {
+proj::GemmShape pick_shape(long long M, int N, int K, int batch, int epi, bool a_f32, bool gathered) {
     struct Cand {
         int bm, bn, depth;
     };
     static const Cand ring[] = {{128, 128, 2}, {64, 128, 3}, {64, 64, 4}, {32, 64, 6}};
     proj::GemmShape t{32, 64, 6, epi};
+    const bool forced = tuned(MLA_TUNE_GEMM_BM) > 0 || tuned(MLA_TUNE_GEMM_BN) > 0 || tuned(MLA_TUNE_GEMM_DEPTH) >= 0;
+    if (M <= 48 && !gathered && !forced && epi != proj::kStoreF16 && (a_f32 ? K == 512 : K == 128 || K == 512 || K == 2048))
+        return {M <= 16 ? 16 : M <= 32 ? 32 : 48, 16, proj::kSkinny, epi};
     const long long need = (long long)cu_count() * 85 / 100;
     if (!a_f32 && N <= 128 && M >= 1024) {
         t = {256, 128, 0, epi};
@@ -134,7 +140,7 @@ int check_weights(const mla_proj_weights *w, bool pre) {
 }
 
 int launch(const GemmArgs &g, int epi, bool a_f32, int batch, hipStream_t s, const char *what) {
-    const proj::GemmShape t = pick_shape(g.M, g.N, batch, epi, a_f32);
+    const proj::GemmShape t = pick_shape(g.M, g.N, g.K, batch, epi, a_f32, g.a_bt != nullptr);
     if (g.n_split < g.N && g.n_split % t.bn != 0)
         return mla::set_error(MLA_ERR_INVALID_ARG, "%s GEMM: column split %d is not a multiple of the tile width %d",
                               what, g.n_split, t.bn);

@@ -115,6 +115,9 @@ hipError_t launch_mha_prefill(const MhaArgs &a, hipStream_t s);
 struct GemmShape {
     int bm, bn, depth, epi;
 };
+// depth of the few-row kernel: bm 16, 32 or 48 covers all rows (M <= bm), bn
+// is not used; K of 128, 512 or 2048, bf16 activations (fp32 with K = 512).
+constexpr int kSkinny = -1;
 
 // The launch covers ceil(M / bm) * ceil(N / bn) tiles x batch, plus
 // g.rope_wgs workgroups of rope / norm rows (four rows each) or g.keys_wgs of

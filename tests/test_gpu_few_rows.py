@@ -1,0 +1,48 @@
+"""Projections of 1 to 49 rows, on either side of the row counts at which the
+few-row GEMM takes another number of row blocks or hands over to the tiled
+kernels, against the oracle at the bounds of the layer tests."""
+import numpy as np
+import pytest
+
+from harness import log
+from oracle import proj_oracle as PO
+import paper_2607_02043_amd as mla
+from paper_2607_02043_amd import workloads as W
+import test_gpu_layer as layer
+
+pytestmark = pytest.mark.gpu
+weights = layer.weights
+
+
+@pytest.mark.parametrize("rows", [1, 2, 15, 16, 17, 32, 33, 48, 49])
+def test_pre_attn_few_rows(rows, weights, monkeypatch):
+    rng = np.random.default_rng(rows)
+    decodes = max(0, rows - 9)
+    case = (list(rng.integers(0, 9000, decodes)) + [100], [1] * decodes + [rows - decodes], 16)
+    monkeypatch.setitem(layer.PRE_CASES, "few", case)
+    layer.test_pre_attn_parity("few", None, weights)
+
+
+@pytest.mark.parametrize("rows", [1, 15, 16, 17, 32, 33, 48, 49])
+@pytest.mark.parametrize("attn_bf16,out_bf16", [(False, False), (True, False), (True, True)])
+def test_post_attn_few_rows(rows, attn_bf16, out_bf16, weights):
+    import torch
+    _, wo, dw = weights
+    log(f"[gpu] post_attn T={rows} attn_bf16={attn_bf16} out_bf16={out_bf16}")
+    a = W.random_attn_out(rows, seed=31)
+    a_dev = torch.from_numpy(a).cuda()
+    if attn_bf16:
+        a_dev = a_dev.to(torch.bfloat16)
+    out = torch.full((rows, 2048), float("nan"), dtype=torch.bfloat16 if out_bf16 else torch.float32, device="cuda")
+    ws = torch.empty(mla.mla_proj_workspace_bytes(rows), dtype=torch.uint8, device="cuda")
+    mla.mla_post_attn(a_dev, dw, out, ws)
+    torch.cuda.synchronize()
+    got = out.float().cpu().numpy().astype(np.float64)
+    ab = PO.through_bf16(a.astype(np.float64))  # what the value up-projection reads
+    o_exact = np.concatenate([ab[:, h] @ wo.w_uv[h].T for h in range(16)], axis=1)
+    up, mags = layer._gemm_bound(o_exact, wo.w_o)
+    exact = o_exact @ wo.w_o.T
+    tol = up + 2.0 ** -16 * mags + (layer._ulp_bf16(exact) if out_bf16 else 0.0)
+    d = np.abs(got - exact)
+    log(f"  out: max |d|/tol = {float((d / tol).max()):.3f}")
+    assert np.isfinite(got).all() and (d <= tol).all()
