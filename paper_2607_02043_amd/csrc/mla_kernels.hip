@@ -191,6 +191,12 @@ __device__ __forceinline__ float wave_sum16(float v) {
 __device__ __forceinline__ int tile_swz(int k) { return k & 7; }
 __device__ __forceinline__ int tile_off(int k, int c) { return (k * kChunksPerRow + (c ^ tile_swz(k))) * 16; }
 
+__device__ __forceinline__ float max3(float x, float y, float z) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
+    return r;
+}
+
 // Transposing LDS read (gfx950): inside each 16-lane group, lane i receives
 // element (i & 3) of the 8 bytes read by lane 4 j + (i >> 2), j = 0..3.
 __device__ __forceinline__ u32x2 lds_read_tr16(const char *p) {
@@ -994,6 +1000,17 @@ __device__ void decode_merge(const AttnArgs &a, int r, int part, float *s_o, flo
 // Per tile: one barrier.  After it, the P*V of tile t and the scores of tile
 // t+1 run back to back (their operands come from different ring slots and P
 // buffers), then the softmax of tile t+1 fills the other P buffer.
+// A tile takes about 4,600 shader clocks, 2,176 of them the products; both
+// waves of a SIMD stand at the same point of it, so what lies between the
+// barrier and the first product, or between two products of a chain, is idle
+// time of the matrix unit.  Hence V is read and converted before the barrier
+// (beside the softmax) and not after it, the rope query operands are read
+// three steps ahead of their products, and the redo test is one comparison
+// per item instead of one per tile: 2048 tokens at prefix 6144 beside 128
+// decode rows 569 -> 555 us, four 1024-token chunks beside 64 rows 546 -> 528.
+// (Waves 4..7 half a tile ahead of the others, with a barrier per half: 561
+// and 548 us.  K operands three steps ahead instead of two: spills, 569 and
+// 560 us.)
 
 // bf16 pairs -> fp16 pairs (exact for |v| in [2^-14, 65504]; larger values
 // clamp to +-65504, smaller ones round toward zero).
@@ -1174,7 +1191,6 @@ __device__ bool chunk_item(const AttnArgs &a, int item, char *smem, int *s_tmp, 
 
     float m_ref = kNegInf, m_lane = kNegInf, l_run = 0.f;
     f32x4 acc[kCT][4];  // [token][value block db]
-    bool bad = false;
 
     // S^T of tile t for this wave's token: lane l, element i of block kb =
     // key 16 kb + 4 g + i of the tile, head hd.  Two accumulation chains.
@@ -1182,7 +1198,7 @@ __device__ bool chunk_item(const AttnArgs &a, int item, char *smem, int *s_tmp, 
         const char *tile = smem + __builtin_amdgcn_readfirstlane(slot * kChunkTileBytes);
         s[0] = s[1] = f32x4{0.f, 0.f, 0.f, 0.f};
         constexpr int D = 2;  // steps whose K operands are in flight
-        u32x4 av[D][2];
+        u32x4 av[D][2], qr[kQSteps - kQRegSteps];
 #pragma unroll
         for (int st = 0; st < D; ++st)
 #pragma unroll
@@ -1197,11 +1213,10 @@ __device__ bool chunk_item(const AttnArgs &a, int item, char *smem, int *s_tmp, 
                     av[st % D][kb] = *reinterpret_cast<const u32x4 *>(tile + kq_off[(st + D) & 1] + 2048 * kb +
                                                                       4096 * ((st + D) >> 1));
             }
-            u32x4 qb;
-            if (st < kQRegSteps)
-                qb = qreg[st];
-            else
-                qb = *reinterpret_cast<const u32x4 *>(s_q + (((st - kQRegSteps) * kCT + wv) * 64 + lane) * 16);
+            if (st >= kQRegSteps - 3 && st < kQSteps - 3)
+                qr[st - (kQRegSteps - 3)] = *reinterpret_cast<const u32x4 *>(
+                    s_q + (((st - (kQRegSteps - 3)) * kCT + wv) * 64 + lane) * 16);
+            const u32x4 qb = st < kQRegSteps ? qreg[st < kQRegSteps ? st : 0] : qr[st < kQRegSteps ? 0 : st - kQRegSteps];
             s[0] = mfma_bf16(cur[0], qb, s[0]);
             s[1] = mfma_bf16(cur[1], qb, s[1]);
             __builtin_amdgcn_sched_barrier(0);
@@ -1219,16 +1234,13 @@ __device__ bool chunk_item(const AttnArgs &a, int item, char *smem, int *s_tmp, 
             for (int e = 0; e < 8; ++e) x[e] = (16 * (e >> 2) + (e & 3) <= rel) ? s[e >> 2][e & 3] : kNegInf;
         }
     };
-    auto lane_max = [&](const float (&x)[8]) {
-        return fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
+    auto lane_max = [&](const float (&x)[8], float m) {
+        return max3(max3(max3(max3(m, x[0], x[1]), x[2], x[3]), x[4], x[5]), x[6], x[7]);
     };
-    auto softmax = [&](int t, int pbuf, const f32x4 (&s)[2], bool main_pass) {
+    auto softmax = [&](int t, int pbuf, const f32x4 (&s)[2]) {
         float x[8];
         masked(t, s, x);
-        const float xm = lane_max(x) * a.scale_log2;
-        m_lane = fmaxf(m_lane, xm);
-        // also true for a first visible key after the first tile
-        bad |= main_pass && xm - m_ref > kMaxPExp;
+        m_lane = lane_max(x, m_lane);
         // the scaled score is rounded before the max is subtracted, so the max
         // key gets p = 1 exactly; masked scores give p = 0
         const float mref = m_ref == kNegInf ? 0.f : m_ref;
@@ -1242,22 +1254,33 @@ __device__ bool chunk_item(const AttnArgs &a, int item, char *smem, int *s_tmp, 
         *reinterpret_cast<u32x4 *>(s_pbuf + __builtin_amdgcn_readfirstlane(pbuf * kPTile) + (wv * 64 + lane) * 16) =
             u32x4{f16x2_bits(p[0], p[1]), f16x2_bits(p[2], p[3]), f16x2_bits(p[4], p[5]), f16x2_bits(p[6], p[7])};
     };
-    // O^T += V^T P^T for tile t (P from buffer t & 1)
-    auto pv = [&](int slot, int pbuf) {
+    // V^T operands of a tile for this wave's value dims, converted to fp16.
+    // They are read and converted before the barrier that P waits for, so
+    // that only the P reads stand between it and the first product.
+    u32x4 av[4];
+    auto vload = [&](int slot) {
         const char *tile = smem + __builtin_amdgcn_readfirstlane(slot * kChunkTileBytes);
+#pragma unroll
+        for (int db = 0; db < 4; ++db) {
+            const u32x2 lo = lds_read_tr16(tile + vt_off[db]);
+            const u32x2 hi = lds_read_tr16(tile + vt_off[db] + 2048);
+            av[db] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto vconv = [&] {
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) av[db][i] = bf16x2_to_f16x2(av[db][i]);
+    };
+    // O^T += V^T P^T for tile t (P from buffer t & 1)
+    auto pv = [&](int pbuf) {
         const char *pb = s_pbuf + __builtin_amdgcn_readfirstlane(pbuf * kPTile) + lane * 16;
         constexpr int PD = 3;  // P operands in flight
         u32x4 bp[PD];
 #pragma unroll
         for (int tb = 0; tb < PD; ++tb) bp[tb] = *reinterpret_cast<const u32x4 *>(pb + tb * 64 * 16);
-        u32x4 av[4];
-#pragma unroll
-        for (int db = 0; db < 4; ++db) {
-            const u32x2 lo = lds_read_tr16(tile + vt_off[db]);
-            const u32x2 hi = lds_read_tr16(tile + vt_off[db] + 2048);
-            av[db] = u32x4{bf16x2_to_f16x2(lo[0]), bf16x2_to_f16x2(lo[1]), bf16x2_to_f16x2(hi[0]),
-                           bf16x2_to_f16x2(hi[1])};
-        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int tb = 0; tb < kCT; ++tb) {
@@ -1294,9 +1317,11 @@ __device__ bool chunk_item(const AttnArgs &a, int item, char *smem, int *s_tmp, 
         if (main_pass) {
             float x[8];
             masked(0, s0, x);
-            m_ref = wave_max16(lane_max(x) * a.scale_log2);
+            m_ref = wave_max16(lane_max(x, kNegInf) * a.scale_log2);
         }
-        softmax(0, 0, s0, main_pass);
+        vload(0);
+        softmax(0, 0, s0);
+        vconv();
     }
     int slot = 0;  // ring slot of tile t (t % 3)
     // steady state: after the barrier, P*V of tile t and the scores of t + 1,
@@ -1305,24 +1330,29 @@ __device__ bool chunk_item(const AttnArgs &a, int item, char *smem, int *s_tmp, 
         TRACE_TILE(t, 11);
         const int next_page = page_of(min(t + 2, ntiles - 1));
         if (t + 1 < ntiles) wait_dma_all();  // tile t + 1 (this wave's part)
-        if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) *s_abort = 1;
         __syncthreads();  // tile t + 1 and P of tile t complete; slot (t + 2) % 3 and P buffer (t + 1) & 1 free
         TRACE_TILE(t, 12);
         const int slot1 = slot == kChunkRing - 1 ? 0 : slot + 1;
         const int slot2 = slot1 == kChunkRing - 1 ? 0 : slot1 + 1;
         if (t + 2 < ntiles) issue(t + 2, slot2, next_page);
         TRACE_TILE(t, 14);
-        pv(slot, t & 1);
+        pv(t & 1);
         TRACE_TILE(t, 15);
         if (t + 1 < ntiles) {
             f32x4 s1[2];
             scores(slot1, s1);
-            softmax(t + 1, (t + 1) & 1, s1, main_pass);
+            vload(slot1);
+            softmax(t + 1, (t + 1) & 1, s1);
+            vconv();
         }
         slot = slot1;
         TRACE_TILE(t, 13);
     }
-    __syncthreads();  // every wave's last flag write and P*V reads are done
+    // a score that exceeds the reference by more than P may hold (also a first
+    // visible key after the first tile): the products are discarded
+    m_lane *= a.scale_log2;
+    if (main_pass && __builtin_amdgcn_ballot_w64(m_lane - m_ref > kMaxPExp) != 0 && lane == 0) *s_abort = 1;
+    __syncthreads();  // every wave's flag write and P*V reads are done
     if (main_pass && __builtin_amdgcn_readfirstlane(*s_abort) != 0) {
         // abandoned: publish the exact maxima for the exact pass
         const float mx = wave_max16(m_lane);
