@@ -80,17 +80,29 @@ int cu_count() {
     return ncu;
 }
 
-// Tile shape of a GEMM launch, from measurements of the layer's GEMMs at 256
-// to 4160 rows: the largest of the LDS-ring tiles 128 x 128 (2 stages),
-// 64 x 128 (3), 64 x 64 (4), 32 x 64 (6) that still gives at least 0.85
-// workgroups per CU (fewer leaves CUs idle; more is a second round of
-// workgroups for large tiles), and the register-staged 256 x 128 tile for the
-// narrow batched value up-projection once it has 1024 rows.  Up to 48 rows
-// (not gathered) take the few-row kernel: before / after attention 17.1 / 14.9 us
-// tiled against 13.0 / 10.9 at 19 rows, 17.3 / 14.8 against 16.3 / 13.2 at 48;
-// at 64 rows it loses, 17.8 / 15.1 against 20.8 / 15.9.  fp32 activations
-// use 64-column tiles.  MLA_GEMM_BM / MLA_GEMM_BN / MLA_GEMM_D override the
-// choice (for tuning; a shape that is not instantiated fails the launch).
+// Tile shape of a GEMM launch, from sweeps over every shape at 49 to 8192 rows
+// (three sets of weights in turn; figures are the call's us before / after the
+// attention).
+//  * Up to 48 rows (not gathered): the few-row kernel.  Tiled against few-row
+//    17.1 / 14.9 : 13.0 / 10.9 at 19 rows, 17.3 / 14.8 : 16.3 / 13.2 at 48; at
+//    64 rows it loses, 17.8 / 15.1 : 20.8 / 15.9.
+//  * Otherwise the largest of the LDS-ring tiles 256 x 256 (2 stages, eight
+//    waves), 128 x 128 (2), 64 x 128 (3), 64 x 64 (4), 32 x 64 (6) that still
+//    gives at least 0.85 workgroups per CU (fewer leaves CUs idle).  The
+//    256 x 256 tile halves the L2 reads but has one workgroup a CU, so its
+//    last round must be as full as that too: at 4160 rows 121 -> 98 before.
+//  * When the tiles fit one round of workgroups, two wave groups share K:
+//    twice the loads in flight per CU.  17.6 -> 16.5 / 15.1 -> 13.4 at 100
+//    rows, 36.9 -> 35.3 / 25.9 -> 24.8 at 1001; with a second round it loses,
+//    27.6 -> 36.1 / 23.3 -> 29.6 at 544.  For the same reason 64 x 64 tiles
+//    that cover 0.6 of the CUs win over a second round of 32 x 64: 19.7 -> 17.1
+//    after at 300 rows.
+//  * The narrow batched value up-projection (N = 128) takes 64 x 128 from 512
+//    rows, register-staged from 1024: 23.6 -> 22.3 after at 544 rows, 80.7 ->
+//    75.9 at 4160 against 256 x 128.
+// fp32 activations use 64-column tiles.  MLA_GEMM_BM / MLA_GEMM_BN / MLA_GEMM_D
+// override the choice (for tuning; a shape that is not instantiated fails the
+// launch).
 proj::GemmShape pick_shape(long long M, int N, int K, int batch, int epi, bool a_f32, bool gathered) {
     struct Cand {
         int bm, bn, depth;
@@ -100,19 +112,28 @@ proj::GemmShape pick_shape(long long M, int N, int K, int batch, int epi, bool a
     const bool forced = tuned(MLA_TUNE_GEMM_BM) > 0 || tuned(MLA_TUNE_GEMM_BN) > 0 || tuned(MLA_TUNE_GEMM_DEPTH) >= 0;
     if (M <= 48 && !gathered && !forced && epi != proj::kStoreF16 && (a_f32 ? K == 512 : K == 128 || K == 512 || K == 2048))
         return {M <= 16 ? 16 : M <= 32 ? 32 : 48, 16, proj::kSkinny, epi};
-    const long long need = (long long)cu_count() * 85 / 100;
+    const long long ncu = cu_count(), need = ncu * 85 / 100;
+    const auto wgs = [&](int bm, int bn) { return (M + bm - 1) / bm * ((N + bn - 1) / bn) * batch; };
+    const long long huge = wgs(256, 256), rounds = (huge + ncu - 1) / ncu;
     if (!a_f32 && N <= 128 && M >= 1024) {
-        t = {256, 128, 0, epi};
+        t = {64, 128, 0, epi};
+    } else if (!a_f32 && N <= 128 && M >= 512) {
+        t = {64, 128, 3, epi};
+    } else if (!a_f32 && !gathered && epi != proj::kStoreF16 && K >= 512 && huge * 100 >= rounds * ncu * 85) {
+        t = {256, 256, 2, epi};
     } else {
         for (const Cand &c : ring) {
             t = {c.bm, c.bn, c.depth, epi};
-            if ((M + c.bm - 1) / c.bm * ((N + c.bn - 1) / c.bn) * batch >= need) break;
+            if (wgs(c.bm, c.bn) >= need) break;
+            if (c.bm == 64 && c.bn == 64 && !a_f32 && K >= 512 && wgs(64, 64) * 10 >= ncu * 6 && wgs(32, 64) > ncu) break;
         }
     }
     if (a_f32) {
         t.bn = proj::kBN;
         t.bm = std::min(t.bm, 128);
     }
+    // two wave groups share K when one round of workgroups covers the tiles
+    if (!forced && !a_f32 && !gathered && t.depth > 0 && t.bm < 256 && K >= 512 && wgs(t.bm, t.bn) <= cu_count()) t.kg = 2;
     if (int v = tuned(MLA_TUNE_GEMM_BM); v > 0) t.bm = v;
     if (!a_f32)
         if (int v = tuned(MLA_TUNE_GEMM_BN); v > 0) t.bn = v;

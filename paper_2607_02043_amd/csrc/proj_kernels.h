@@ -109,11 +109,13 @@ hipError_t launch_mha_prefill(const MhaArgs &a, hipStream_t s);
 // picks the LDS ring fed by direct loads with that many stages, 0 the
 // register-staged kernel.  Instantiated: ring, bn 64 with (bm, depth) (32, 6),
 // (64, 4), (128, 3); ring, bn 128 with (32, 4), (64, 3), (128, 2), (128, 3);
+// ring, (256, 256, 2) on eight waves (no side job, no fp16 output);
 // register-staged (bm, bn) (128, 256) and (256, 128) on eight waves, (32,
 // 128), (64, 128), (128, 128) on four.  fp32 activations use bn = 64 and any
 // bm of 32, 64, 128 (N a multiple of 64).
 struct GemmShape {
     int bm, bn, depth, epi;
+    int kg = 1;  // wave groups sharing K (ring kernels: 1 or 2)
 };
 // depth of the few-row kernel: bm 16, 32 or 48 covers all rows (M <= bm), bn
 // is not used; K of 128, 512 or 2048, bf16 activations (fp32 with K = 512).

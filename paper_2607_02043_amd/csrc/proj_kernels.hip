@@ -4,13 +4,16 @@
 //
 // GEMM: C = A . B^T with both operands K-contiguous (activations [M][K],
 // weights [N][K] as the model stores them), bf16 MFMA 16x16x32 with fp32
-// accumulation.  A workgroup of four waves computes a BM x 64 tile; each wave
-// a (BM / 2) x 32 block.  K advances 64 at a time through a ring of D LDS
-// stages that direct global -> LDS loads fill D - 1 stages ahead, so that a
-// workgroup keeps several round trips to HBM in flight (one stage in flight
-// leaves the loop waiting a full memory latency per 64 of K).  A variant for
-// fp32 activations converts them to bf16 in registers on the way to LDS
-// (two stages, register staged).
+// accumulation.  The products are taken as B . A^T, so that a lane holds
+// neighbouring columns of one row and stores 16 bytes at a time (two-byte
+// stores before: the calls before the attention 45.1 -> 36.9 us at 1001 rows,
+// 117 -> 101 at 4160).  Tiled kernels advance K 64 at a time through a ring of
+// LDS stages that direct global -> LDS loads fill ahead, so that a workgroup
+// keeps several round trips to memory in flight (one stage in flight leaves
+// the loop waiting a full memory latency per 64 of K), or through registers;
+// a variant for fp32 activations converts them to bf16 in registers on the
+// way to LDS (two stages, register staged).  Few rows have a kernel without
+// LDS staging.
 #include "proj_kernels.h"
 
 namespace proj {
@@ -37,6 +40,16 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 // an MFMA operand read touches, and the 2 rows x 8 chunks of 16 consecutive
 // lanes of a store pass, land on 16 distinct bank groups.
 __device__ __forceinline__ int slot(int row, int kc) { return row * 8 + (kc ^ ((row >> 1) & 7)); }
+
+// B rows are read in another order: lane l of a 16-column block pair (32
+// columns) takes column 8 (l / 4) + 4 b + l % 4 of block b, so that the
+// products of both blocks give a lane 8 consecutive columns of one row to store.
+// Their swizzle uses the row bits in which those 16 rows differ.
+__device__ __forceinline__ int swz_b(int row) { return ((row >> 1) & 1) | (((row >> 3) & 3) << 1); }
+__device__ __forceinline__ int slot_b(int row, int kc) { return row * 8 + (kc ^ swz_b(row)); }
+__device__ __forceinline__ int col_of_lane(int lane, int nb) {
+    return 32 * (nb >> 1) + 8 * ((lane & 15) >> 2) + 4 * (nb & 1) + (lane & 3);
+}
 
 // One 16-byte global -> LDS load per lane: lane i writes LDS bytes
 // [lds + 16 i, lds + 16 i + 16); `lds` must be wave-uniform.  Completion is
@@ -83,22 +96,56 @@ __device__ __forceinline__ void store_one(const GemmArgs &g, float v, int row, i
     }
 }
 
-// Stores of one tile.  acc[mb][nb][i] = C[rbase + 16 mb + i][cbase + 16 nb];
-// columns at or past N are not stored.
+// Eight consecutive columns n .. n + 7 of row `row` (n a multiple of 8; heads,
+// column ranges and N are multiples of 8 too, so they share one destination).
+template <int EPI>
+__device__ __forceinline__ void store_eight(const GemmArgs &g, f32x4 x, f32x4 y, int row, int n, int z) {
+    const auto bf16x8_store = [&](uint16_t *dst) {
+        *reinterpret_cast<u32x4 *>(dst) = u32x4{pack2(x[0], x[1]), pack2(x[2], x[3]), pack2(y[0], y[1]), pack2(y[2], y[3])};
+    };
+    const auto f32x8_store = [&](float *dst) {
+        *reinterpret_cast<f32x4 *>(dst) = x;
+        *reinterpret_cast<f32x4 *>(dst + 4) = y;
+    };
+    if constexpr (EPI == kStoreBf16) {
+        bf16x8_store(static_cast<uint16_t *>(g.c) + z * g.c_bstride + (long long)row * g.ldc + n);
+    } else if constexpr (EPI == kStoreF32) {
+        f32x8_store(static_cast<float *>(g.c) + z * g.c_bstride + (long long)row * g.ldc + n);
+    } else if constexpr (EPI == kStoreF16) {
+        typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+        const f16x8 h = {(_Float16)x[0], (_Float16)x[1], (_Float16)x[2], (_Float16)x[3],
+                         (_Float16)y[0], (_Float16)y[1], (_Float16)y[2], (_Float16)y[3]};
+        *reinterpret_cast<f16x8 *>(static_cast<_Float16 *>(g.c) + z * g.c_bstride + (long long)row * g.ldc + n) = h;
+    } else {
+        if (n < kQCols) {
+            const int h = n / kQkHead, j = n - h * kQkHead;
+            if (j < kNope)
+                bf16x8_store(g.qn + ((long long)row * kHeads + h) * kNope + j);
+            else
+                f32x8_store(g.qpe + ((long long)row * kHeads + h) * kRope + j - kNope);
+        } else {
+            f32x8_store(g.kvf + (long long)row * kDqk + n - kQCols);
+        }
+    }
+}
+
+// Stores of one tile (products taken as B . A^T): acc[mb][2 p + b][i] =
+// C[rbase + 16 mb + lane % 16][cbase + 32 p + 8 (lane / 16) + 4 b + i]; columns
+// at or past N are not stored.  The outputs of a step are up to 68 MB (the
+// absorbed queries), written 16 bytes a lane and 64 to 128 bytes a row.
 template <int EPI, int MB, int NB>
 __device__ __forceinline__ void store_tile(const GemmArgs &g, const f32x4 (&acc)[MB][NB], int rbase, int cbase,
                                            int z) {
+    static_assert(NB % 2 == 0, "column blocks come in pairs");
+    const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
+        const int row = rbase + mb * 16 + (lane & 15);
+        if (row >= g.M) continue;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = rbase + mb * 16 + i;
-            if (row >= g.M) continue;
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int n = cbase + nb * 16;
-                if (n < g.N) store_one<EPI>(g, acc[mb][nb][i], row, n, z);
-            }
+        for (int p = 0; p < NB / 2; ++p) {
+            const int n = cbase + 32 * p + 8 * (lane >> 4);
+            if (n < g.N) store_eight<EPI>(g, acc[mb][2 * p], acc[mb][2 * p + 1], row, n, z);
         }
     }
 }
@@ -226,19 +273,24 @@ __device__ __forceinline__ bool is_rope_wg(const GemmArgs &g, int BM, int BN) {
 }
 
 // bf16 activations.  D-stage LDS ring filled by direct loads; four waves in
-// a 2 x 2 grid, each computing a (BM / 2) x (BN / 2) block.
-template <int BM, int BN, int D, int EPI>
-__global__ __launch_bounds__(256) void gemm_ring_kernel(const GemmArgs g) {
+// a 2 x 2 grid, each computing a (BM / 2) x (BN / 2) block.  KG = 2: eight
+// waves, the second four on every other 64 of K through a ring of their own;
+// the two partial tiles meet in LDS at the end.
+template <int BM, int BN, int D, int KG, int EPI, int WR = 2, int WC = 2>
+__global__ __launch_bounds__(64 * WR * WC * KG) void gemm_ring_kernel(const GemmArgs g) {
     constexpr int ROWS = BM + BN;            // A rows then B rows of a stage
     constexpr int STAGE = ROWS * 8;          // 16-byte slots per stage
-    constexpr int NPW = STAGE / 64 / 4;      // loads per wave per stage
-    constexpr int WM = BM / 2, MB = WM / 16;
-    constexpr int WN = BN / 2, NB = WN / 16;
-    static_assert(STAGE % 256 == 0, "a stage must split evenly over four waves");
-    __shared__ __attribute__((aligned(1024))) u32x4 ring[D * STAGE];
+    constexpr int NW = WR * WC;              // waves of a group
+    constexpr int NPW = STAGE / 64 / NW;     // loads per wave per stage
+    constexpr int WM = BM / WR, MB = WM / 16;
+    constexpr int WN = BN / WC, NB = WN / 16;
+    static_assert(STAGE % (64 * NW) == 0, "a stage must split evenly over the waves");
+    __shared__ __attribute__((aligned(1024))) u32x4 ring_all[KG * D * STAGE];
 
     if (is_rope_wg(g, BM, BN)) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) % NW;
+    const int kg = KG > 1 ? __builtin_amdgcn_readfirstlane(tid / (64 * NW)) : 0;
+    u32x4 *const ring = ring_all + kg * D * STAGE;
     int m0, n0;
     tile_of(g.M, g.N, BM, BN, &m0, &n0);
     const int z = blockIdx.z;
@@ -253,7 +305,7 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(const GemmArgs g) {
     for (int i = 0; i < NPW; ++i) {
         const int s = (wave * NPW + i) * 64 + lane;
         const int row = s >> 3;
-        const int kc = (s & 7) ^ ((row >> 1) & 7);
+        const int kc = (s & 7) ^ (row < BM ? (row >> 1) & 7 : swz_b(row));
         if (row < BM) {
             const int r = min(m0 + row, g.M - 1);
             long long ar = r;
@@ -268,17 +320,17 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(const GemmArgs g) {
                     ar = ((long long)pg << g.a_log2p) + (r & ((1 << g.a_log2p) - 1));
                 }
             }
-            src[i] = abase + z * g.a_bstride + ar * g.lda + kc * 8;
+            src[i] = abase + z * g.a_bstride + ar * g.lda + kc * 8 + kg * kBK;
         } else {
             const int n = min(n0 + row - BM, g.N - 1) - nbase;
-            src[i] = bseg + z * g.b_bstride + (long long)n * g.ldb + kc * 8;
+            src[i] = bseg + z * g.b_bstride + (long long)n * g.ldb + kc * 8 + kg * kBK;
         }
     }
     const uint32_t ring_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(ring));
     auto issue = [&](int st) {
         const uint32_t dst = ring_lds + (uint32_t)((st % D) * STAGE * 16 + wave * NPW * 1024);
 #pragma unroll
-        for (int i = 0; i < NPW; ++i) dma16(src[i] + st * kBK, __builtin_amdgcn_readfirstlane(dst + i * 1024));
+        for (int i = 0; i < NPW; ++i) dma16(src[i] + st * (KG * kBK), __builtin_amdgcn_readfirstlane(dst + i * 1024));
     };
 
     f32x4 acc[MB][NB];
@@ -286,9 +338,9 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(const GemmArgs g) {
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int wr = (wave >> 1) * WM;       // wave's first A row in the stage
-    const int wc = BM + (wave & 1) * WN;   // wave's first B row in the stage
-    const int nk = g.K / kBK;
+    const int wr = (wave / WC) * WM;       // wave's first A row in the stage
+    const int wc = BM + (wave % WC) * WN;   // wave's first B row in the stage
+    const int nk = g.K / (KG * kBK);
 
 #pragma unroll
     for (int st = 0; st < D - 1; ++st)
@@ -306,15 +358,31 @@ __global__ __launch_bounds__(256) void gemm_ring_kernel(const GemmArgs g) {
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) fa[mb] = cur[slot(wr + mb * 16 + (lane & 15), kc)];
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) fb[nb] = cur[slot(wc + nb * 16 + (lane & 15), kc)];
+            for (int nb = 0; nb < NB; ++nb) fb[nb] = cur[slot_b(wc + col_of_lane(lane, nb), kc)];
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma(fa[mb], fb[nb], acc[mb][nb]);
+                for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma(fb[nb], fa[mb], acc[mb][nb]);
         }
         __syncthreads();  // the slot of stage kt is refilled by the next iteration's load
     }
-    store_tile<EPI, MB, NB>(g, acc, m0 + wr + 4 * (lane >> 4), n0 + (wave & 1) * WN + (lane & 15), z);
+    if constexpr (KG > 1) {
+        f32x4 *const part = reinterpret_cast<f32x4 *>(ring_all) + wave * MB * NB * 64 + lane;
+        static_assert(NW * MB * NB * 64 <= KG * D * STAGE, "the partial tile fits the rings");
+        if (kg != 0) {
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) part[(mb * NB + nb) * 64] = acc[mb][nb];
+        }
+        __syncthreads();
+        if (kg != 0) return;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[mb][nb] += part[(mb * NB + nb) * 64];
+    }
+    store_tile<EPI, MB, NB>(g, acc, m0 + wr, n0 + (wave % WC) * WN, z);
 }
 
 // bf16 activations, register-staged: each thread loads its share of the
@@ -350,7 +418,7 @@ __global__ __launch_bounds__(64 * WR * WC) void gemm_reg_kernel(const GemmArgs g
     for (int i = 0; i < LPT; ++i) {
         const int c = tid + NT * i;
         const int row = c >> 3, kc = c & 7;
-        dst[i] = slot(row, kc);
+        dst[i] = row < BM ? slot(row, kc) : slot_b(row, kc);
         if (row < BM) {
             const int r = min(m0 + row, g.M - 1);
             src[i] = static_cast<const uint16_t *>(g.a) + z * g.a_bstride + (long long)r * g.lda + kc * 8;
@@ -385,11 +453,11 @@ __global__ __launch_bounds__(64 * WR * WC) void gemm_reg_kernel(const GemmArgs g
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) fa[mb] = cur[slot(wr + mb * 16 + (lane & 15), kc)];
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) fb[nb] = cur[slot(wc + nb * 16 + (lane & 15), kc)];
+            for (int nb = 0; nb < NB; ++nb) fb[nb] = cur[slot_b(wc + col_of_lane(lane, nb), kc)];
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma(fa[mb], fb[nb], acc[mb][nb]);
+                for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma(fb[nb], fa[mb], acc[mb][nb]);
         }
     };
 
@@ -414,7 +482,7 @@ __global__ __launch_bounds__(64 * WR * WC) void gemm_reg_kernel(const GemmArgs g
         if (kt + 2 < nk) store(r0, 0);
         __syncthreads();
     }
-    store_tile<EPI, MB, NB>(g, acc, m0 + wr + 4 * (lane >> 4), n0 + (wc - BM) + (lane & 15), z);
+    store_tile<EPI, MB, NB>(g, acc, m0 + wr, n0 + (wc - BM), z);
 }
 
 // fp32 activations, converted to bf16 (nearest even) in registers; two LDS
@@ -463,7 +531,7 @@ __global__ __launch_bounds__(256) void gemm_f32a_kernel(const GemmArgs g) {
             s[slot(crow + 32 * i, ckc)] = u32x4{pack2(x.x, x.y), pack2(x.z, x.w), pack2(y.x, y.y), pack2(y.z, y.w)};
         }
 #pragma unroll
-        for (int i = 0; i < 2; ++i) s[slot(BM + crow + 32 * i, ckc)] = rb[i];
+        for (int i = 0; i < 2; ++i) s[slot_b(BM + crow + 32 * i, ckc)] = rb[i];
     };
 
     f32x4 acc[MB][2];
@@ -486,16 +554,16 @@ __global__ __launch_bounds__(256) void gemm_f32a_kernel(const GemmArgs g) {
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) fa[mb] = cur[slot(wr + mb * 16 + (lane & 15), kc)];
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb) fb[nb] = cur[slot(wc + nb * 16 + (lane & 15), kc)];
+            for (int nb = 0; nb < 2; ++nb) fb[nb] = cur[slot_b(wc + col_of_lane(lane, nb), kc)];
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = mfma(fa[mb], fb[nb], acc[mb][nb]);
+                for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = mfma(fb[nb], fa[mb], acc[mb][nb]);
         }
         if (kt + 1 < nk) store(sm[(kt + 1) & 1]);
         __syncthreads();
     }
-    store_tile<EPI, MB, 2>(g, acc, m0 + wr + 4 * (lane >> 4), n0 + (wave & 1) * 32 + (lane & 15), z);
+    store_tile<EPI, MB, 2>(g, acc, m0 + wr, n0 + (wave & 1) * 32, z);
 }
 
 // Few rows (M <= 16 MB, MB <= 3): the call is bound by reading the weights once,
@@ -817,12 +885,31 @@ __global__ __launch_bounds__(64 * kMhaWaves) void mha_prefill_kernel(const MhaAr
     }
 }
 
+template <int BM, int BN, int D, int KG>
+hipError_t launch_ring_kg(const GemmArgs &g, int epi, dim3 grid, hipStream_t s) {
+    if (epi == kStoreF16) gemm_ring_kernel<BM, BN, D, KG, kStoreF16><<<grid, 256 * KG, 0, s>>>(g);
+    else if (epi == kStoreBf16) gemm_ring_kernel<BM, BN, D, KG, kStoreBf16><<<grid, 256 * KG, 0, s>>>(g);
+    else if (epi == kStoreF32) gemm_ring_kernel<BM, BN, D, KG, kStoreF32><<<grid, 256 * KG, 0, s>>>(g);
+    else if (epi == kQkvSplit) gemm_ring_kernel<BM, BN, D, KG, kQkvSplit><<<grid, 256 * KG, 0, s>>>(g);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
 template <int BM, int BN, int D>
-hipError_t launch_ring(const GemmArgs &g, int epi, dim3 grid, hipStream_t s) {
-    if (epi == kStoreF16) gemm_ring_kernel<BM, BN, D, kStoreF16><<<grid, 256, 0, s>>>(g);
-    else if (epi == kStoreBf16) gemm_ring_kernel<BM, BN, D, kStoreBf16><<<grid, 256, 0, s>>>(g);
-    else if (epi == kStoreF32) gemm_ring_kernel<BM, BN, D, kStoreF32><<<grid, 256, 0, s>>>(g);
-    else if (epi == kQkvSplit) gemm_ring_kernel<BM, BN, D, kQkvSplit><<<grid, 256, 0, s>>>(g);
+hipError_t launch_ring(const GemmArgs &g, const GemmShape &t, dim3 grid, hipStream_t s) {
+    if (t.kg == 2) {
+        if constexpr (2 * D * (BM + BN) * kBK * 2 <= 160 * 1024)
+            if (g.K % (2 * kBK) == 0 && g.rope_wgs == 0 && g.keys_wgs == 0) return launch_ring_kg<BM, BN, D, 2>(g, t.epi, grid, s);
+        return hipErrorInvalidValue;
+    }
+    return launch_ring_kg<BM, BN, D, 1>(g, t.epi, grid, s);
+}
+
+// 256 x 256 tiles on eight waves (128 x 64 each), two 64 KB stages.
+hipError_t launch_ring_256(const GemmArgs &g, int epi, dim3 grid, hipStream_t s) {
+    if (g.rope_wgs != 0 || g.keys_wgs != 0 || g.a_bt != nullptr) return hipErrorInvalidValue;
+    if (epi == kStoreBf16) gemm_ring_kernel<256, 256, 2, 1, kStoreBf16, 2, 4><<<grid, 512, 0, s>>>(g);
+    else if (epi == kStoreF32) gemm_ring_kernel<256, 256, 2, 1, kStoreF32, 2, 4><<<grid, 512, 0, s>>>(g);
+    else if (epi == kQkvSplit) gemm_ring_kernel<256, 256, 2, 1, kQkvSplit, 2, 4><<<grid, 512, 0, s>>>(g);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
@@ -910,16 +997,17 @@ hipError_t launch_gemm(const GemmArgs &g, const GemmShape &t, bool a_f32, int ba
     switch (key) {
         case 128 * 1000 + 256 * 10 + 0: return launch_reg<128, 256, 2, 4>(g, t.epi, grid, s);
         case 256 * 1000 + 128 * 10 + 0: return launch_reg<256, 128, 4, 2>(g, t.epi, grid, s);
+        case 256 * 1000 + 256 * 10 + 2: return launch_ring_256(g, t.epi, grid, s);
         case 128 * 1000 + 128 * 10 + 0: return launch_reg<128, 128, 2, 2>(g, t.epi, grid, s);
         case 64 * 1000 + 128 * 10 + 0: return launch_reg<64, 128, 2, 2>(g, t.epi, grid, s);
         case 32 * 1000 + 128 * 10 + 0: return launch_reg<32, 128, 2, 2>(g, t.epi, grid, s);
-        case 32 * 1000 + 64 * 10 + 6: return launch_ring<32, 64, 6>(g, t.epi, grid, s);
-        case 64 * 1000 + 64 * 10 + 4: return launch_ring<64, 64, 4>(g, t.epi, grid, s);
-        case 128 * 1000 + 64 * 10 + 3: return launch_ring<128, 64, 3>(g, t.epi, grid, s);
-        case 32 * 1000 + 128 * 10 + 4: return launch_ring<32, 128, 4>(g, t.epi, grid, s);
-        case 64 * 1000 + 128 * 10 + 3: return launch_ring<64, 128, 3>(g, t.epi, grid, s);
-        case 128 * 1000 + 128 * 10 + 2: return launch_ring<128, 128, 2>(g, t.epi, grid, s);
-        case 128 * 1000 + 128 * 10 + 3: return launch_ring<128, 128, 3>(g, t.epi, grid, s);
+        case 32 * 1000 + 64 * 10 + 6: return launch_ring<32, 64, 6>(g, t, grid, s);
+        case 64 * 1000 + 64 * 10 + 4: return launch_ring<64, 64, 4>(g, t, grid, s);
+        case 128 * 1000 + 64 * 10 + 3: return launch_ring<128, 64, 3>(g, t, grid, s);
+        case 32 * 1000 + 128 * 10 + 4: return launch_ring<32, 128, 4>(g, t, grid, s);
+        case 64 * 1000 + 128 * 10 + 3: return launch_ring<64, 128, 3>(g, t, grid, s);
+        case 128 * 1000 + 128 * 10 + 2: return launch_ring<128, 128, 2>(g, t, grid, s);
+        case 128 * 1000 + 128 * 10 + 3: return launch_ring<128, 128, 3>(g, t, grid, s);
         default: return hipErrorInvalidValue;
     }
 }

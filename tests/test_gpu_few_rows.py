@@ -1,6 +1,8 @@
 """Projections of 1 to 49 rows, on either side of the row counts at which the
 few-row GEMM takes another number of row blocks or hands over to the tiled
-kernels, against the oracle at the bounds of the layer tests."""
+kernels, against the oracle at the bounds of the layer tests; then the tiles
+that the library picks for more rows against a forced tile that those tests
+compare with the oracle."""
 import numpy as np
 import pytest
 
@@ -46,3 +48,39 @@ def test_post_attn_few_rows(rows, attn_bf16, out_bf16, weights):
     d = np.abs(got - exact)
     log(f"  out: max |d|/tol = {float((d / tol).max()):.3f}")
     assert np.isfinite(got).all() and (d <= tol).all()
+
+
+@pytest.mark.parametrize("rows", [49, 64, 65, 130, 257, 300, 512, 545, 1024, 3700])
+def test_picked_tiles_equal_forced_tiles(rows, weights):
+    """Both accumulate the same products in fp32 in another order, so a stored
+    bf16 value moves by one step where it lies next to a rounding boundary.
+    With at most 1 % of the values moving (the bound of the layer tests), by at
+    most 2^-7 of themselves, the 2-norm of the difference stays below 2^-7
+    sqrt(0.01) = 8e-4 of the result's, and so do the sums over moved inputs."""
+    import torch
+    _, _, dw = weights
+    log(f"[gpu] picked against forced tiles, {rows} rows")
+    batch = W.make_batch([17, 100], [1, rows - 1], 64, 3)
+    db = mla.DeviceBatch.from_batch(batch)
+    hidden = layer.to_dev(W.random_hidden(rows, seed=5))
+    attn = torch.from_numpy(W.random_attn_out(rows, seed=6)).cuda()
+    ws = torch.empty(mla.mla_proj_workspace_bytes(rows), dtype=torch.uint8, device="cuda")
+
+    def run():
+        q = torch.empty((rows, 16, 576), dtype=torch.bfloat16, device="cuda")
+        lat = torch.empty((rows, 576), dtype=torch.bfloat16, device="cuda")
+        outs = [torch.empty((rows, 2048), dtype=dt, device="cuda") for dt in (torch.float32, torch.bfloat16, torch.float32)]
+        mla.mla_pre_attn(db, hidden, dw, q, lat, ws)
+        for a, o in zip((attn, attn, attn.to(torch.bfloat16)), outs):
+            mla.mla_post_attn(a, dw, o, ws)
+        torch.cuda.synchronize()
+        return [q, lat, *outs]
+
+    picked = run()
+    with mla.tuned({mla.TUNE_GEMM_BM: 64, mla.TUNE_GEMM_BN: 64, mla.TUNE_GEMM_DEPTH: 4}):
+        forced = run()
+    for k, (x, y) in enumerate(zip(picked, forced)):
+        assert torch.isfinite(x).all()
+        d = float((x.double() - y.double()).norm() / y.double().norm())
+        log(f"  output {k}: {d:.2e}")
+        assert d <= 8e-4
