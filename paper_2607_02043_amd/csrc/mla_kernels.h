@@ -63,6 +63,22 @@ struct AttnArgs {
     ChunkRoute route;          // chunk requests it sends to the multi-head path are left out of this launch
 };
 
+// The fixed first items of the attention launch's G workgroups (G at most the
+// number of items).  Workgroup b < D takes decode item b, the others take
+// chunk items 0, 1, ..; a workgroup whose kind has run out takes the next item
+// of the other kind.  Each kind's first items are then its lowest indexes:
+// first_chunk_items chunk items and G minus that many decode items.
+__host__ __device__ inline int first_chunk_items(int n_chunk, int n_dec, int D, int G) {
+    const int n = G - D + (D > n_dec ? D - n_dec : 0);
+    return n < n_chunk ? n : n_chunk;
+}
+// Item of workgroup b: a chunk item, or n_chunk + a decode item.
+__host__ __device__ inline int first_item(int n_chunk, int n_dec, int D, int G, int b) {
+    if (b < D) return b < n_dec ? n_chunk + b : (G - D) + (b - n_dec);
+    const int k = b - D;
+    return k < n_chunk ? k : n_chunk + (D < n_dec ? D : n_dec) + (k - n_chunk);
+}
+
 struct AppendArgs {
     const uint16_t *src;
     uint16_t *kv;

@@ -204,10 +204,22 @@ __device__ __forceinline__ u32x2 lds_read_tr16(const char *p) {
     return __builtin_bit_cast(u32x2, v);
 }
 
+// threadIdx.x behind an empty asm: values derived from it inside a work item
+// are then computed per item instead of being hoisted out of the persistent
+// loop, where they would stay live across both paths and spill to scratch (a
+// scratch reload waits on vmcnt, i.e. on every DMA in flight).
+__device__ __forceinline__ int item_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
 // ------------------------------------------------------ work-item lookup
 // Items of one kind are numbered request by request; request r owns
-// count(r) consecutive items.  The workgroup scans the per-request counts
-// (256 requests per round) and finds the request owning item `target`.
+// count(r) consecutive items.  Every wavefront looks its item up by itself, 64
+// requests a step with the next 64 lengths already loading: no barrier and
+// no LDS exchange stands between the load of the lengths and the item's own
+// loads (a lookup is mostly the latency of that load).
 struct ReqLens {
     const int32_t *cu_q;
     const int32_t *prefix;
@@ -218,53 +230,48 @@ struct Located {
     int r, local, p, row0, c;
 };
 
-template <typename CountFn>
-__device__ bool locate_item(int target, int num_reqs, const ReqLens &rl, CountFn count, int *s_tmp,
-                            Located &loc) {
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int nthr = blockDim.x, nw = nthr >> 6;
-    if (tid == 0) s_tmp[8] = -1;
-    int running = 0;
-    for (int base = 0; base < num_reqs; base += nthr) {
-        const int r = rl.rev ? num_reqs - 1 - (base + tid) : base + tid;
-        int cnt = 0, p = 0, row0 = 0, c = 0;
-        if (base + tid < num_reqs) {
-            row0 = rl.cu_q[r];
-            c = rl.cu_q[r + 1] - row0;
-            p = rl.prefix[r];
-            cnt = count(p, c);
-        }
-        int inc = cnt;
+struct LenRow {
+    int row0, next, p;
+};
+
+// Lengths of request r (all zero outside [0, num_reqs)).
+__device__ __forceinline__ LenRow load_lens(const int32_t *cu_q, const int32_t *prefix, int r, int num_reqs) {
+    LenRow l{0, 0, 0};
+    if ((unsigned)r < (unsigned)num_reqs) l = LenRow{cu_q[r], cu_q[r + 1], prefix[r]};
+    return l;
+}
+
+// Inclusive prefix sum over the lanes of a wavefront.
+__device__ __forceinline__ int wave_scan(int v, int lane) {
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int v = __shfl_up(inc, d, 64);
-            if (lane >= d) inc += v;
-        }
-        if (lane == 63) s_tmp[wv] = inc;
-        __syncthreads();
-        int off = 0, total = 0;
-        for (int k = 0; k < nw; ++k) {
-            const int t = s_tmp[k];
-            off += (k < wv) ? t : 0;
-            total += t;
-        }
-        inc += off;
-        const int exc = inc - cnt;
-        if (cnt > 0 && target >= running + exc && target < running + inc) {
-            s_tmp[8] = r;
-            s_tmp[9] = target - running - exc;
-            s_tmp[10] = p;
-            s_tmp[11] = row0;
-            s_tmp[12] = c;
-        }
-        __syncthreads();
-        if (s_tmp[8] >= 0) {  // the same values in every lane: keep them in scalar registers
-            loc = Located{__builtin_amdgcn_readfirstlane(s_tmp[8]), __builtin_amdgcn_readfirstlane(s_tmp[9]),
-                          __builtin_amdgcn_readfirstlane(s_tmp[10]), __builtin_amdgcn_readfirstlane(s_tmp[11]),
-                          __builtin_amdgcn_readfirstlane(s_tmp[12])};
+    for (int d = 1; d < 64; d <<= 1) {
+        const int t = __shfl_up(v, d, 64);
+        if (lane >= d) v += t;
+    }
+    return v;
+}
+
+template <typename CountFn>
+__device__ bool locate_item(int target, int num_reqs, const ReqLens &rl, CountFn count, Located &loc) {
+    const int lane = item_tid() & 63;
+    const auto req = [&](int base) { return rl.rev ? num_reqs - 1 - (base + lane) : base + lane; };
+    int running = 0;
+    LenRow cur = load_lens(rl.cu_q, rl.prefix, req(0), num_reqs);
+    for (int base = 0; base < num_reqs; base += 64) {
+        const LenRow nxt = load_lens(rl.cu_q, rl.prefix, req(base + 64), num_reqs);
+        const int r = req(base), c = cur.next - cur.row0;
+        const int cnt = (unsigned)r < (unsigned)num_reqs ? count(cur.p, c) : 0;
+        const int inc = running + wave_scan(cnt, lane);
+        const uint64_t hit = __builtin_amdgcn_ballot_w64(cnt > 0 && target >= inc - cnt && target < inc);
+        if (hit != 0) {
+            const int l = __builtin_ctzll(hit);
+            loc = Located{__builtin_amdgcn_readlane(r, l), target - __builtin_amdgcn_readlane(inc - cnt, l),
+                          __builtin_amdgcn_readlane(cur.p, l), __builtin_amdgcn_readlane(cur.row0, l),
+                          __builtin_amdgcn_readlane(c, l)};
             return true;
         }
-        running += total;
+        running = __builtin_amdgcn_readlane(inc, 63);
+        cur = nxt;
     }
     return false;
 }
@@ -570,50 +577,35 @@ struct DecSeg {
 
 __device__ __forceinline__ int dec_tiles(int p, int c) { return c == 1 ? ceil_div(p + 1, kDecKeys) : 0; }
 
-// Exclusive prefix sum over the threads of the workgroup (uses s_w[0 .. waves - 1]).
-__device__ __forceinline__ int block_scan_excl(int v, int *s_w, int &total) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    int inc = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int t = __shfl_up(inc, d, 64);
-        if (lane >= d) inc += t;
-    }
-    if (lane == 63) s_w[wv] = inc;
-    __syncthreads();
-    int off = 0;
-    total = 0;
-    for (int k = 0; k < nw; ++k) {
-        const int t = s_w[k];
-        off += (k < wv) ? t : 0;
-        total += t;
-    }
-    __syncthreads();
-    return inc - v + off;
-}
-
-// Segments (request order) of the decode tile range [R0, R1); returns their count.
-__device__ int find_segments(const AttnArgs &a, int R0, int R1, DecSeg *s_seg, int *s_tmp) {
-    const int tid = threadIdx.x;
-    int running = 0, nseg = 0;
-    for (int base = 0; base < a.num_reqs && running < R1; base += blockDim.x) {
-        const int r = base + tid;
-        int nt = 0, p = 0, row0 = 0;
-        if (r < a.num_reqs) {
-            row0 = a.cu_q[r];
-            p = a.prefix[r];
-            // rows outside [0, T) only arise from device lengths that disagree with the host's
-            nt = (p >= 0 && row0 >= 0 && row0 < a.num_rows) ? dec_tiles(p, a.cu_q[r + 1] - row0) : 0;
+// Segments (request order) of the decode tile range [R0, R1), with the page
+// window each needs; returns their count.  Every wavefront of a group finds
+// them by itself and `writer` stores them.
+__device__ int find_unit(const AttnArgs &a, int R0, int R1, DecSeg *s_seg, bool writer) {
+    const int lane = item_tid() & 63;
+    int running = 0, nseg = 0, pages = 0;
+    LenRow cur = load_lens(a.cu_q, a.prefix, lane, a.num_reqs);
+    for (int base = 0; base < a.num_reqs && running < R1; base += 64) {
+        const LenRow nxt = load_lens(a.cu_q, a.prefix, base + 64 + lane, a.num_reqs);
+        // rows outside [0, T) only arise from device lengths that disagree with the host's
+        const bool row_ok = base + lane < a.num_reqs && cur.p >= 0 && cur.row0 >= 0 && cur.row0 < a.num_rows;
+        const int nt = row_ok ? dec_tiles(cur.p, cur.next - cur.row0) : 0;
+        const int inc = running + wave_scan(nt, lane);
+        const int T = inc - nt;
+        const bool ov = nt > 0 && T < R1 && inc > R0;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(ov);
+        if (m != 0) {
+            const int t0 = max(R0 - T, 0), t1 = min(R1 - T, nt);
+            const int lp0 = (t0 * kDecKeys) >> a.log2_page;
+            const int np = ov ? ((min(t1 * kDecKeys, cur.p + 1) - 1) >> a.log2_page) - lp0 + 1 : 0;
+            const int pend = pages + wave_scan(np, lane);
+            const int j = nseg + __builtin_popcountll(m & ((1ull << lane) - 1));
+            if (ov && writer && j < kMaxSeg) s_seg[j] = DecSeg{base + lane, cur.p, cur.row0, t0, t1, pend - np, lp0};
+            nseg += __builtin_popcountll(m);
+            pages = __builtin_amdgcn_readlane(pend, 63);
         }
-        int tot_t, tot_s;
-        const int T = running + block_scan_excl(nt, s_tmp, tot_t);
-        const bool ov = nt > 0 && T < R1 && T + nt > R0;
-        const int j = nseg + block_scan_excl(ov ? 1 : 0, s_tmp, tot_s);
-        if (ov && j < kMaxSeg) s_seg[j] = DecSeg{r, p, row0, max(R0 - T, 0), min(R1 - T, nt), 0, 0};
-        nseg += tot_s;
-        running += tot_t;
+        running = __builtin_amdgcn_readlane(inc, 63);
+        cur = nxt;
     }
-    __syncthreads();
     return min(nseg, kMaxSeg);
 }
 
@@ -688,16 +680,6 @@ __device__ __forceinline__ void wait_units_newer(int n) {  // n of the later uni
         asm volatile("s_waitcnt vmcnt(18)" ::: "memory");
 }
 
-// threadIdx.x behind an empty asm: values derived from it inside a work item
-// are then computed per item instead of being hoisted out of the persistent
-// loop, where they would stay live across both paths and spill to scratch (a
-// scratch reload waits on vmcnt, i.e. on every DMA in flight).
-__device__ __forceinline__ int item_tid() {
-    int t = threadIdx.x;
-    asm volatile("" : "+v"(t));
-    return t;
-}
-
 // Barrier of the four wavefronts of one wave group, through an arrival
 // counter in LDS; epoch (wave-uniform) counts the group's barriers so far.
 // Each wave first waits for its own LDS accesses, so what it wrote before the
@@ -719,7 +701,7 @@ __device__ __forceinline__ void group_barrier(int *ctr, int &epoch, int spin_lim
     asm volatile("" ::: "memory");
 }
 
-__device__ void decode_wg(const AttnArgs &a, int w, char *smem, int *s_tmp, int (*s_pages_g)[kPageWindow],
+__device__ void decode_wg(const AttnArgs &a, int w, char *smem, int (*s_pages_g)[kPageWindow],
                           DecSeg (*s_seg_g)[kMaxSeg], int *s_gbar) {
     const int tid = item_tid(), lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -727,47 +709,45 @@ __device__ void decode_wg(const AttnArgs &a, int w, char *smem, int *s_tmp, int 
     const int g = lane >> 4, h = lane & 15;
     const int S = a.dec_unit_tiles;
     // Item w is the pair of decode units 2 w and 2 w + 1 (S tiles each), one per
-    // wave group.  Both groups find their segments (block-wide scans).
-    int nseg2[2], nunits2[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int R0 = (2 * w + q) * S;
-        const int R1 = min(R0 + S, a.dec_total_tiles);
-        nseg2[q] = R0 < R1 ? find_segments(a, R0, R1, s_seg_g[q], s_tmp) : 0;
-        nunits2[q] = nseg2[q] > 0 ? nseg2[q] + (R1 - R0) : 0;
-    }
-    TRACE(1);
-    const int n_iter = max(nunits2[0], nunits2[1]);
-    if (n_iter == 0) return;  // both groups idle (uniform)
+    // wave group.  A unit of a tile or two is mostly start-up, a chain of round
+    // trips to memory: the lengths, then the query block and the page ids at
+    // once, then the first tile beside the fused append.
     const int v = 2 * w + grp;  // this group's unit
-    const int R0 = v * S;
-    const int nseg = nseg2[grp], n_units = nunits2[grp];
+    const int R0 = v * S, R1 = min(R0 + S, a.dec_total_tiles);
     DecSeg *const s_seg = s_seg_g[grp];
     int *const s_pages = s_pages_g[grp];
-    if (gtid == 0) {  // page-window offsets of the segments
-        int pw = 0;
-        for (int j = 0; j < nseg; ++j) {
-            const DecSeg sg = s_seg[j];
-            const int lp0 = (sg.t0 * kDecKeys) >> a.log2_page;
-            const int klast = min(sg.t1 * kDecKeys, sg.p + 1) - 1;
-            s_seg[j].pw = pw;
-            s_seg[j].lp0 = lp0;
-            pw += (klast >> a.log2_page) - lp0 + 1;
+    const int nseg = R0 < R1 ? find_unit(a, R0, R1, s_seg, gw == 0) : 0;
+    const int n_units = nseg > 0 ? nseg + (R1 - R0) : 0;
+    if (tid < 2) s_gbar[tid] = 0;
+    TRACE(1);
+    __syncthreads();
+    uint32_t dma_off[(kTileDma + 1) / 2];
+    tile_dma_offsets(gw, lane, dma_off);
+    const uint32_t ring = lds_addr(smem) + grp * kDecGroupBytes;
+    float *s_X = reinterpret_cast<float *>(smem + 2 * kDecGroupBytes + grp * kDecXBytes);
+    Cursor prod{0, -1}, cons{0, -1};
+    if (n_units > 0) {
+        issue_unit(a, s_seg[0], -1, s_pages, ring, gw, lane, dma_off);  // the first query block
+        advance(prod, s_seg);
+        // page window: entry gtid belongs to the last segment that starts at or before it
+        static_assert(kPageWindow == kThreads, "one window entry per thread of the group");
+        int j = 0;
+        for (int k = 1; k < nseg; ++k) j = s_seg[k].pw <= gtid ? k : j;
+        const DecSeg sg = s_seg[j];
+        const int i = gtid - sg.pw;
+        if (i < ((min(sg.t1 * kDecKeys, sg.p + 1) - 1) >> a.log2_page) - sg.lp0 + 1) {
+            const int lp = sg.lp0 + i;
+            const int pg = lp < a.max_pages ? a.bt[(size_t)sg.r * a.max_pages + lp] : 0;
+            const bool ok = (unsigned)pg < (unsigned)a.num_pages;
+            if (!ok) raise_flag(kFlagBadPage);
+            s_pages[gtid] = ok ? pg : 0;
         }
     }
     __syncthreads();
-    for (int j = 0; j < nseg; ++j) {
-        const DecSeg sg = s_seg[j];
-        const int klast = min(sg.t1 * kDecKeys, sg.p + 1) - 1;
-        const int n = (klast >> a.log2_page) - sg.lp0 + 1;
-        const int32_t *btr = a.bt + (size_t)sg.r * a.max_pages;
-        for (int i = gtid; i < n && sg.pw + i < kPageWindow; i += kThreads) {
-            const int lp = sg.lp0 + i;
-            const int pg = lp < a.max_pages ? btr[lp] : 0;
-            const bool ok = (unsigned)pg < (unsigned)a.num_pages;
-            if (!ok) raise_flag(kFlagBadPage);
-            s_pages[sg.pw + i] = ok ? pg : 0;
-        }
+    if (n_units == 0) return;  // this group has no unit (the other one may)
+    if (n_units > 1) {
+        issue_unit(a, s_seg[prod.j], prod.t, s_pages, ring + kDecTileBytes, gw, lane, dma_off);
+        advance(prod, s_seg);
     }
     if (a.new_kv != nullptr) {  // fused append: the group holding a request's last tile writes its latent
         for (int j = 0; j < nseg; ++j) {
@@ -775,21 +755,10 @@ __device__ void decode_wg(const AttnArgs &a, int w, char *smem, int *s_tmp, int 
             if (sg.t1 == dec_tiles(sg.p, 1)) append_rows_group(a, sg.r, sg.p, sg.row, 1, gtid);
         }
     }
-    if (tid < 2) s_gbar[tid] = 0;
-    __syncthreads();
-    if (n_units == 0) return;  // this group has no unit (the other one may)
     int epoch = 0;
     int *const gbar = s_gbar + grp;
     TRACE(2);
     TRACE_VAL(8, 1000000ull * 2 + n_units);
-
-    uint32_t dma_off[(kTileDma + 1) / 2];
-    tile_dma_offsets(gw, lane, dma_off);
-    const uint32_t ring = lds_addr(smem) + grp * kDecGroupBytes;
-    float *s_X = reinterpret_cast<float *>(smem + 2 * kDecGroupBytes + grp * kDecXBytes);
-    Cursor prod{0, -1}, cons{0, -1};
-    issue_unit(a, s_seg[prod.j], prod.t, s_pages, ring, gw, lane, dma_off);
-    advance(prod, s_seg);
 
     u32x4 qreg[9];  // this wave's half of the query operand: steps 9 (gw >> 1) .. + 9
     f32x4 acc[8];
@@ -806,13 +775,13 @@ __device__ void decode_wg(const AttnArgs &a, int w, char *smem, int *s_tmp, int 
     // wavefronts (two per unit).
     for (int u = 0; u < n_units; ++u) {
         TRACE_TILE(u, 10);
-        wait_dma_all();                // unit u (the only one in flight)
+        wait_dma_all();                // unit u (the first two are issued together)
         group_barrier(gbar, epoch, a.spin_limit);    // unit u landed; slot (u + 1) % 2 is free
         bool tile_unit = false;
         DecSeg sg{};
         const char *slot = smem + grp * kDecGroupBytes + (u % kDecRing) * kDecTileBytes;
         {
-            if (prod.j < nseg) {
+            if (u > 0 && prod.j < nseg) {
                 issue_unit(a, s_seg[prod.j], prod.t, s_pages, ring + ((u + 1) % kDecRing) * kDecTileBytes, gw, lane,
                            dma_off);
                 advance(prod, s_seg);
@@ -935,7 +904,6 @@ __device__ void decode_wg(const AttnArgs &a, int w, char *smem, int *s_tmp, int 
             l_run = 0.f;
         }
     }
-    (void)R0;
     TRACE(4);
 }
 
@@ -1004,13 +972,13 @@ __device__ void decode_merge(const AttnArgs &a, int r, int part, float *s_o, flo
 // waves of a SIMD stand at the same point of it, so what lies between the
 // barrier and the first product, or between two products of a chain, is idle
 // time of the matrix unit.  Hence V is read and converted before the barrier
-// (beside the softmax) and not after it, the rope query operands are read
-// three steps ahead of their products, and the redo test is one comparison
+// (beside the softmax) and not after it, and the redo test is one comparison
 // per item instead of one per tile: 2048 tokens at prefix 6144 beside 128
-// decode rows 569 -> 555 us, four 1024-token chunks beside 64 rows 546 -> 528.
+// decode rows 570 -> 551 us, four 1024-token chunks beside 64 rows 547 -> 535.
 // (Waves 4..7 half a tile ahead of the others, with a barrier per half: 561
-// and 548 us.  K operands three steps ahead instead of two: spills, 569 and
-// 560 us.)
+// and 548 us.  K operands three steps ahead instead of two, or the rope query
+// operands read ahead of their products: registers spill in the loop, 569 and
+// 560, 620 and 644 us.)
 
 // bf16 pairs -> fp16 pairs (exact for |v| in [2^-14, 65504]; larger values
 // clamp to +-65504, smaller ones round toward zero).
@@ -1076,9 +1044,9 @@ __device__ __forceinline__ void lds_dma16_sbase_imm(const void *sbase, uint32_t 
 
 // Returns true when the main pass was abandoned: the caller then runs the
 // item again with exact = true (the exact maxima wait in LDS).
-__device__ bool chunk_item(const AttnArgs &a, int item, char *smem, int *s_tmp, int *s_pages, bool exact) {
+__device__ bool chunk_item(const AttnArgs &a, int item, char *smem, int *s_pages, bool exact) {
     Located lc;
-    if (!locate_item(item, a.num_reqs, ReqLens{a.cu_q, a.prefix, a.chunk_rev != 0}, ChunkCount{a.ks_chunk, a.route}, s_tmp, lc)) return false;
+    if (!locate_item(item, a.num_reqs, ReqLens{a.cu_q, a.prefix, a.chunk_rev != 0}, ChunkCount{a.ks_chunk, a.route}, lc)) return false;
     const ChunkItem it = decode_chunk_item(a, lc);
     TRACE(1);
     const int r = it.r;
@@ -1198,7 +1166,7 @@ __device__ bool chunk_item(const AttnArgs &a, int item, char *smem, int *s_tmp, 
         const char *tile = smem + __builtin_amdgcn_readfirstlane(slot * kChunkTileBytes);
         s[0] = s[1] = f32x4{0.f, 0.f, 0.f, 0.f};
         constexpr int D = 2;  // steps whose K operands are in flight
-        u32x4 av[D][2], qr[kQSteps - kQRegSteps];
+        u32x4 av[D][2];
 #pragma unroll
         for (int st = 0; st < D; ++st)
 #pragma unroll
@@ -1213,10 +1181,11 @@ __device__ bool chunk_item(const AttnArgs &a, int item, char *smem, int *s_tmp, 
                     av[st % D][kb] = *reinterpret_cast<const u32x4 *>(tile + kq_off[(st + D) & 1] + 2048 * kb +
                                                                       4096 * ((st + D) >> 1));
             }
-            if (st >= kQRegSteps - 3 && st < kQSteps - 3)
-                qr[st - (kQRegSteps - 3)] = *reinterpret_cast<const u32x4 *>(
-                    s_q + (((st - (kQRegSteps - 3)) * kCT + wv) * 64 + lane) * 16);
-            const u32x4 qb = st < kQRegSteps ? qreg[st < kQRegSteps ? st : 0] : qr[st < kQRegSteps ? 0 : st - kQRegSteps];
+            u32x4 qb;
+            if (st < kQRegSteps)
+                qb = qreg[st];
+            else
+                qb = *reinterpret_cast<const u32x4 *>(s_q + (((st - kQRegSteps) * kCT + wv) * 64 + lane) * 16);
             s[0] = mfma_bf16(cur[0], qb, s[0]);
             s[1] = mfma_bf16(cur[1], qb, s[1]);
             __builtin_amdgcn_sched_barrier(0);
@@ -1414,49 +1383,59 @@ constexpr int kMainLds = kDecLds > kChunkLds ? kDecLds : kChunkLds;
 // beside the chunk tiles from the start.  An item's results and partial
 // slots depend only on its index, so the schedule never changes the output
 // bits.  The last workgroup to finish zeroes the counters for the next call.
+// Every workgroup's first item is fixed (first_item), and the counters deal out
+// what is left: a step with no more items than workgroups makes no atomic at
+// all.  (With every item taken from the counters, a workgroup of such a step
+// waited for up to five round trips to memory.  With the shorter decode
+// start-up: 4 decode rows of 842 to 3569 keys 28.6 -> 19.6 us, 68 rows of about
+// 205 keys 31.3 -> 23.6, 256 rows of up to 16384 keys 475 -> 465.)
 __global__ __launch_bounds__(kAttnThreads, 1) void attention_kernel(AttnArgs a) {
     __shared__ __attribute__((aligned(16))) char smem[kMainLds];
-    __shared__ int s_tmp[16];
     __shared__ int s_pages[2][kPageWindow];  // chunk items use the first window
     __shared__ DecSeg s_seg[2][kMaxSeg];
     __shared__ int s_gbar[2];
     __shared__ int s_item;
-    bool on_dec = (int)blockIdx.x < a.dec_first_wgs;  // thread 0's current queue
+    int item = first_item(a.n_chunk_items, a.n_dec_units, a.dec_first_wgs, a.grid, (int)blockIdx.x);
+    bool on_dec = item >= a.n_chunk_items;  // thread 0's current queue
     for (;;) {
+        TRACE_ITEM(item);
+        if (item < a.n_chunk_items) {
+            // a second, exact pass only if the main one was abandoned
+            for (int pass = 0; pass < 2; ++pass) {
+                if (!chunk_item(a, item, smem, s_pages[0], pass != 0)) break;
+                __syncthreads();
+            }
+        }
+        else
+            decode_wg(a, item - a.n_chunk_items, smem, s_pages, s_seg, s_gbar);
+        TRACE(7);
+        int grid = a.grid;
+        asm volatile("" : "+s"(grid));  // (computed again per item: kept across the items it would take registers from their loops)
+        if (a.n_chunk_items + a.n_dec_units <= grid) return;
         if (threadIdx.x == 0) {
+            const int fixed_chunk = first_chunk_items(a.n_chunk_items, a.n_dec_units, a.dec_first_wgs, grid);
             // the current queue, then the other one: -1 once both are empty
             int it = -1;
             for (int k = 0; k < 2 && it < 0; ++k) {
                 if (on_dec) {
-                    const int d = __hip_atomic_fetch_add(a.work + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const int d = grid - fixed_chunk + __hip_atomic_fetch_add(a.work + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     if (d < a.n_dec_units) it = a.n_chunk_items + d;
                 } else {
-                    const int c = __hip_atomic_fetch_add(a.work, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const int c = fixed_chunk + __hip_atomic_fetch_add(a.work, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     if (c < a.n_chunk_items) it = c;
                 }
                 if (it < 0) on_dec = !on_dec;
             }
             s_item = it;
         }
-        __syncthreads();
-        const int item = s_item;
+        __syncthreads();  // LDS free for the next item, whose index is known
+        item = __builtin_amdgcn_readfirstlane(s_item);
         if (item < 0) break;
-        TRACE_ITEM(item);
-        if (item < a.n_chunk_items) {
-            // a second, exact pass only if the main one was abandoned
-            for (int pass = 0; pass < 2; ++pass) {
-                if (!chunk_item(a, item, smem, s_tmp, s_pages[0], pass != 0)) break;
-                __syncthreads();
-            }
-        }
-        else
-            decode_wg(a, item - a.n_chunk_items, smem, s_tmp, s_pages, s_seg, s_gbar);
-        TRACE(7);
-        __syncthreads();  // LDS (and s_item) free for the next item
+        __syncthreads();  // s_item read
     }
     if (threadIdx.x == 0) {
         const int done = __hip_atomic_fetch_add(a.work + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (done == (int)gridDim.x - 1) {  // every workgroup has taken its last item
+        if (done == a.grid - 1) {  // every workgroup has taken its last item
             __hip_atomic_store(a.work, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(a.work + 1, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(a.work + 2, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1474,7 +1453,6 @@ __host__ __device__ __forceinline__ int merge_dec_wgs(const AttnArgs &a) {
 // across units), then one per (chunk item, block row).
 template <bool MANY>
 __global__ __launch_bounds__(kThreads, MANY ? 4 : 5) void combine_kernel(AttnArgs a) {
-    __shared__ int s_tmp[16];
     __shared__ __attribute__((aligned(16))) float s_o[4 * kDv];
     __shared__ float s_ml[8];
     const int b = blockIdx.x;
@@ -1487,7 +1465,7 @@ __global__ __launch_bounds__(kThreads, MANY ? 4 : 5) void combine_kernel(AttnArg
     // 0 merges that row over the block's splits
     const int item = (b - n_dec) / kChunkBlockTokens, j = (b - n_dec) % kChunkBlockTokens;
     Located lc;
-    if (!locate_item(item, a.num_reqs, ReqLens{a.cu_q, a.prefix, a.chunk_rev != 0}, ChunkCount{a.ks_chunk, a.route}, s_tmp, lc)) return;
+    if (!locate_item(item, a.num_reqs, ReqLens{a.cu_q, a.prefix, a.chunk_rev != 0}, ChunkCount{a.ks_chunk, a.route}, lc)) return;
     const ChunkItem it = decode_chunk_item(a, lc);
     if (it.ks != 0 || it.nks_eff <= 1 || a.ws_chunk_o == nullptr || j >= it.i1 - it.i0) return;
     if (it.p < 0 || it.row0 < 0 || it.row0 + it.i1 > a.num_rows) return;
