@@ -595,18 +595,27 @@ __device__ int find_unit(const AttnArgs &a, int R0, int R1, DecSeg *s_seg, bool 
     return min(nseg, kMaxSeg);
 }
 
-// Unit cursor of a workgroup's stream: segment j, tile t (t < 0: the query block).
+// Unit cursor of a group's stream: segment j, tile t (t < 0: the query block).
+// The segment is kept in scalar registers and read from LDS only when it
+// changes, so that no LDS round trip stands before a tile's loads (256 rows of
+// up to 16384 keys 465.1 -> 461.7 us, 19 rows of about 5430 keys 62.8 -> 61.8).
 struct Cursor {
     int j, t;
+    DecSeg sg;
 };
-__device__ __forceinline__ void advance(Cursor &c, const DecSeg *s_seg) {
-    if (c.t < 0)
-        c.t = s_seg[c.j].t0;
-    else
-        ++c.t;
-    if (c.t >= s_seg[c.j].t1) {
+__device__ __forceinline__ DecSeg load_seg(const DecSeg *s_seg, int j) {
+    const DecSeg d = s_seg[j];
+    return DecSeg{__builtin_amdgcn_readfirstlane(d.r),  __builtin_amdgcn_readfirstlane(d.p),
+                  __builtin_amdgcn_readfirstlane(d.row), __builtin_amdgcn_readfirstlane(d.t0),
+                  __builtin_amdgcn_readfirstlane(d.t1), __builtin_amdgcn_readfirstlane(d.pw),
+                  __builtin_amdgcn_readfirstlane(d.lp0)};
+}
+__device__ __forceinline__ void advance(Cursor &c, const DecSeg *s_seg, int nseg) {
+    c.t = c.t < 0 ? c.sg.t0 : c.t + 1;
+    if (c.t >= c.sg.t1) {
         ++c.j;
         c.t = -1;
+        if (c.j < nseg) c.sg = load_seg(s_seg, c.j);
     }
 }
 
@@ -714,10 +723,12 @@ __device__ void decode_wg(const AttnArgs &a, int w, char *smem, int (*s_pages_g)
     tile_dma_offsets(gw, lane, dma_off);
     const uint32_t ring = lds_addr(smem) + grp * kDecGroupBytes;
     float *s_X = reinterpret_cast<float *>(smem + 2 * kDecGroupBytes + grp * kDecXBytes);
-    Cursor prod{0, -1}, cons{0, -1};
+    Cursor prod{0, -1, DecSeg{}};
+    if (n_units > 0) prod.sg = load_seg(s_seg, 0);
+    Cursor cons = prod;
     if (n_units > 0) {
-        issue_unit(a, s_seg[0], -1, s_pages, ring, gw, lane, dma_off);  // the first query block
-        advance(prod, s_seg);
+        issue_unit(a, prod.sg, -1, s_pages, ring, gw, lane, dma_off);  // the first query block
+        advance(prod, s_seg, nseg);
         // page window: entry gtid belongs to the last segment that starts at or before it
         static_assert(kPageWindow == kThreads, "one window entry per thread of the group");
         int j = 0;
@@ -735,8 +746,8 @@ __device__ void decode_wg(const AttnArgs &a, int w, char *smem, int (*s_pages_g)
     __syncthreads();
     if (n_units == 0) return;  // this group has no unit (the other one may)
     if (n_units > 1) {
-        issue_unit(a, s_seg[prod.j], prod.t, s_pages, ring + kDecTileBytes, gw, lane, dma_off);
-        advance(prod, s_seg);
+        issue_unit(a, prod.sg, prod.t, s_pages, ring + kDecTileBytes, gw, lane, dma_off);
+        advance(prod, s_seg, nseg);
     }
     if (a.new_kv != nullptr) {  // fused append: the group holding a request's last tile writes its latent
         for (int j = 0; j < nseg; ++j) {
@@ -767,20 +778,18 @@ __device__ void decode_wg(const AttnArgs &a, int w, char *smem, int (*s_pages_g)
         wait_dma_all();                // unit u (the first two are issued together)
         group_barrier(gbar, epoch, a.spin_limit);    // unit u landed; slot (u + 1) % 2 is free
         bool tile_unit = false;
-        DecSeg sg{};
+        const DecSeg sg = cons.sg;
         const char *slot = smem + grp * kDecGroupBytes + (u % kDecRing) * kDecTileBytes;
         {
             if (u > 0 && prod.j < nseg) {
-                issue_unit(a, s_seg[prod.j], prod.t, s_pages, ring + ((u + 1) % kDecRing) * kDecTileBytes, gw, lane,
-                           dma_off);
-                advance(prod, s_seg);
+                issue_unit(a, prod.sg, prod.t, s_pages, ring + ((u + 1) % kDecRing) * kDecTileBytes, gw, lane, dma_off);
+                advance(prod, s_seg, nseg);
             }
-            sg = s_seg[cons.j];
             if (cons.t < 0) {  // a new request: its query block
 #pragma unroll
                 for (int s2 = 0; s2 < 9; ++s2)
                     qreg[s2] = *reinterpret_cast<const u32x4 *>(slot + (h * kChunksPerRow + (9 * hf + s2) * 4 + g) * 16);
-                advance(cons, s_seg);
+                advance(cons, s_seg, nseg);
             } else {
                 tile_unit = true;
                 TRACE_TILE(u, 11);
@@ -867,7 +876,7 @@ __device__ void decode_wg(const AttnArgs &a, int w, char *smem, int (*s_pages_g)
 
         TRACE_TILE(u, 14);
         const int jseg = cons.j;
-        advance(cons, s_seg);
+        advance(cons, s_seg, nseg);
         if (cons.j != jseg) {  // the segment's last tile: finish it
             const float l_tot = wave_sum16(l_run);
             if (sg.t0 == 0 && sg.t1 == dec_tiles(sg.p, 1)) {
