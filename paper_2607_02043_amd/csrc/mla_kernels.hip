@@ -191,11 +191,10 @@ __device__ __forceinline__ float wave_sum16(float v) {
 __device__ __forceinline__ int tile_swz(int k) { return k & 7; }
 __device__ __forceinline__ int tile_off(int k, int c) { return (k * kChunksPerRow + (c ^ tile_swz(k))) * 16; }
 
-__device__ __forceinline__ float max3(float x, float y, float z) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
-    return r;
-}
+// One v_max3_f32.  Written with fmaxf and not as inline assembly: its operands
+// are MFMA results, and the wait states such a read needs are only inserted for
+// instructions the compiler knows.
+__device__ __forceinline__ float max3(float x, float y, float z) { return fmaxf(fmaxf(x, y), z); }
 
 // Transposing LDS read (gfx950): inside each 16-lane group, lane i receives
 // element (i & 3) of the 8 bytes read by lane 4 j + (i >> 2), j = 0..3.
