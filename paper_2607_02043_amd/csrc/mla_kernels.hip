@@ -1509,6 +1509,9 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendArgs a) {
     const u32x4 va = src[lane];
     u32x4 vb = {0u, 0u, 0u, 0u};
     if (lane < kChunksPerRow - 64) vb = src[64 + lane];
+    // rows past the device's last request (device lengths shorter than the
+    // host's) belong to nobody: skipped, with the flag raised
+    const int total = a.cu_q[a.num_reqs];
     int r, start, pr;
     if (a.num_reqs <= 64) {
         const int cw = lane < a.num_reqs ? a.cu_q[lane] : INT_MAX;
@@ -1524,7 +1527,7 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendArgs a) {
     }
     const int t = pr + (row - start);
     const int lp = t >> a.log2_page;
-    const int page = t >= 0 && lp < a.max_pages ? a.bt[(size_t)r * a.max_pages + lp] : -1;
+    const int page = row < total && t >= 0 && lp < a.max_pages ? a.bt[(size_t)r * a.max_pages + lp] : -1;
     if ((unsigned)page >= (unsigned)a.num_pages) {
         raise_flag(kFlagBadPage);
         return;

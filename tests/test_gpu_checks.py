@@ -3,6 +3,7 @@
 * Ordinary workloads leave the device flags clear.
 * A block-table entry outside the pool is never dereferenced: the kernels
   raise MLA_FLAG_BAD_PAGE, and the rest of the pool is left as it was.
+* Rows past the end of the device lengths are not appended anywhere.
 * Check mode rejects, before launching: such an entry, device lengths that
   differ from the host ones, and written slots aliased between requests.
 * An expired bounded wait raises MLA_FLAG_WAIT_EXPIRED; the condition is
@@ -57,6 +58,29 @@ def test_bad_page_id_raises_the_flag(debug):
         # entry stands for were never written anywhere
         pool = g.pool_np()
         assert pool.shape == li.pool.shape
+
+
+@pytest.mark.parametrize("reqs", [3, 64, 70])
+def test_append_skips_rows_past_the_device_lengths(reqs, debug):
+    """Device row offsets that end two rows before the host's: those rows belong
+    to no request, so the append leaves the pool alone for them and raises the flag."""
+    rng = np.random.default_rng(reqs)
+    wl = W.custom(rng.integers(0, 40, reqs), [1] * (reqs - 1) + [4], page_size=16, seed=reqs, name="short device lengths")
+    b, li = wl.batch, wl.layer(0)
+    db = mla.DeviceBatch.from_batch(b)
+    db.cu_q_dev[-1] -= 2
+    log(f"[gpu] append, {reqs} requests, two rows past the device lengths")
+    g = GpuLayer(db, li)
+    mla.append_latent_kv(db, g.new, g.pool)
+    assert mla.device_flags() & mla.MLA_FLAG_BAD_PAGE
+    want = li.pool.copy()
+    row = 0
+    for r in range(reqs):
+        for i in range(int(b.q_lens[r]) - (2 if r == reqs - 1 else 0)):
+            t = int(b.prefix_lens[r]) + i
+            want[b.block_table[r, t // 16], t % 16] = li.new_latents.reshape(-1, W.D_QK)[row + i]
+        row += int(b.q_lens[r])
+    assert np.array_equal(g.pool_np().reshape(want.shape), want)
 
 
 def test_check_mode_rejects_bad_batches(debug):
