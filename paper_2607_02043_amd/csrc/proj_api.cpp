@@ -102,7 +102,10 @@ int cu_count() {
 //    75.9 at 4160 against 256 x 128.
 // fp32 activations use 64-column tiles.  MLA_GEMM_BM / MLA_GEMM_BN / MLA_GEMM_D
 // override the choice (for tuning; a shape that is not instantiated fails the
-// launch).
+// launch).  Where only one or two are set the others keep the plain choice, the
+// largest ring tile that covers the CUs (256 x 128 register-staged for the
+// up-projection from 1024 rows): its neighbours are instantiated, those of the
+// shapes above are not.
 proj::GemmShape pick_shape(long long M, int N, int K, int batch, int epi, bool a_f32, bool gathered) {
     struct Cand {
         int bm, bn, depth;
@@ -116,16 +119,16 @@ proj::GemmShape pick_shape(long long M, int N, int K, int batch, int epi, bool a
     const auto wgs = [&](int bm, int bn) { return (M + bm - 1) / bm * ((N + bn - 1) / bn) * batch; };
     const long long huge = wgs(256, 256), rounds = (huge + ncu - 1) / ncu;
     if (!a_f32 && N <= 128 && M >= 1024) {
-        t = {64, 128, 0, epi};
-    } else if (!a_f32 && N <= 128 && M >= 512) {
+        t = {forced ? 256 : 64, 128, 0, epi};
+    } else if (!forced && !a_f32 && N <= 128 && M >= 512) {
         t = {64, 128, 3, epi};
-    } else if (!a_f32 && !gathered && epi != proj::kStoreF16 && K >= 512 && huge * 100 >= rounds * ncu * 85) {
+    } else if (!forced && !a_f32 && !gathered && epi != proj::kStoreF16 && K >= 512 && huge * 100 >= rounds * ncu * 85) {
         t = {256, 256, 2, epi};
     } else {
         for (const Cand &c : ring) {
             t = {c.bm, c.bn, c.depth, epi};
             if (wgs(c.bm, c.bn) >= need) break;
-            if (c.bm == 64 && c.bn == 64 && !a_f32 && K >= 512 && wgs(64, 64) * 10 >= ncu * 6 && wgs(32, 64) > ncu) break;
+            if (!forced && c.bm == 64 && c.bn == 64 && !a_f32 && K >= 512 && wgs(64, 64) * 10 >= ncu * 6 && wgs(32, 64) > ncu) break;
         }
     }
     if (a_f32) {
