@@ -45,7 +45,6 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -152,11 +151,6 @@ __device__ __forceinline__ void lds_dma16(const void *gsrc, uint32_t lds_base) {
 
 __device__ __forceinline__ void wait_dma_all() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ void wait_dma_keep9() { asm volatile("s_waitcnt vmcnt(9)" ::: "memory"); }
-
-// vmcnt(0) with expcnt / lgkmcnt left alone (gfx9 s_waitcnt encoding),
-// issued through the builtin so the compiler's scoreboard accounts for it
-// and inserts no vmcnt wait of its own inside the pipelined loops.
-__device__ __forceinline__ void wait_vm_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 __device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
@@ -376,36 +370,6 @@ __device__ __forceinline__ void append_rows_group(const AttnArgs &a, int r, int 
         *reinterpret_cast<u32x4 *>(a.kv_out + ((size_t)page * a.page_size + (key & (a.page_size - 1))) * kDqk +
                                    c * 8) = v;
     }
-}
-
-// Scores of 16 keys (tile rows key_base .. key_base + 15) against one token's
-// query operand: lane l gets S[key_base + 4 (l/16) + i][head l%16], i = 0..3.
-// Reads are staged 6 steps at a time; two accumulation chains.
-__device__ __forceinline__ f32x4 score16(const char *tile, int key_base, const u32x4 *qreg, int lane) {
-    const int g = lane >> 4, key = key_base + (lane & 15);
-    f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-    constexpr int G = 6;
-#pragma unroll
-    for (int grp = 0; grp < 18 / G; ++grp) {
-        u32x4 av[G];
-#pragma unroll
-        for (int j = 0; j < G; ++j)
-            av[j] = *reinterpret_cast<const u32x4 *>(tile + tile_off(key, (grp * G + j) * 4 + g));
-#pragma unroll
-        for (int j = 0; j < G; j += 2) {
-            acc0 = mfma_bf16(av[j], qreg[grp * G + j], acc0);
-            acc1 = mfma_bf16(av[j + 1], qreg[grp * G + j + 1], acc1);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x100, G, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, G, 0);
-    }
-    return acc0 + acc1;
-}
-
-__device__ __forceinline__ void load_query(const AttnArgs &a, int row, int lane, u32x4 *qreg) {
-    const uint16_t *qp = a.q + ((size_t)row * kHeads + (lane & 15)) * kDqk + (lane >> 4) * 8;
-#pragma unroll
-    for (int st = 0; st < 18; ++st) qreg[st] = *reinterpret_cast<const u32x4 *>(qp + st * 32);
 }
 
 // Store 4 consecutive dims of one (row, head) output, fp32 or bf16.
@@ -663,15 +627,6 @@ __device__ __forceinline__ void issue_unit(const AttnArgs &a, const DecSeg &sg, 
     }
 #pragma unroll
     for (int i = 0; i < kDma; ++i) lds_dma16(src[i], __builtin_amdgcn_readfirstlane(slot + (i * 4 + wv) * 1024));
-}
-
-__device__ __forceinline__ void wait_units_newer(int n) {  // n of the later units may stay in flight
-    if (n <= 0)
-        wait_dma_all();
-    else if (n == 1)
-        wait_dma_keep9();
-    else
-        asm volatile("s_waitcnt vmcnt(18)" ::: "memory");
 }
 
 // Barrier of the four wavefronts of one wave group, through an arrival

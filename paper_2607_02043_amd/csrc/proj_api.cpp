@@ -113,7 +113,8 @@ proj::GemmShape pick_shape(long long M, int N, int K, int batch, int epi, bool a
     static const Cand ring[] = {{128, 128, 2}, {64, 128, 3}, {64, 64, 4}, {32, 64, 6}};
     proj::GemmShape t{32, 64, 6, epi};
     const bool forced = tuned(MLA_TUNE_GEMM_BM) > 0 || tuned(MLA_TUNE_GEMM_BN) > 0 || tuned(MLA_TUNE_GEMM_DEPTH) >= 0;
-    if (M <= 48 && !gathered && !forced && epi != proj::kStoreF16 && (a_f32 ? K == 512 : K == 128 || K == 512 || K == 2048))
+    const bool few_k = K == 2048 ? !a_f32 && epi != proj::kStoreF16 : epi == proj::kStoreBf16 && (K == 512 || (K == 128 && !a_f32));
+    if (M <= 48 && !gathered && !forced && few_k)
         return {M <= 16 ? 16 : M <= 32 ? 32 : 48, 16, proj::kSkinny, epi};
     const long long ncu = cu_count(), need = ncu * 85 / 100;
     const auto wgs = [&](int bm, int bn) { return (M + bm - 1) / bm * ((N + bn - 1) / bn) * batch; };

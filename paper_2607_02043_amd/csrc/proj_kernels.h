@@ -112,13 +112,16 @@ hipError_t launch_mha_prefill(const MhaArgs &a, hipStream_t s);
 // ring, (256, 256, 2) on eight waves (no side job, no fp16 output);
 // register-staged (bm, bn) (128, 256) and (256, 128) on eight waves, (32,
 // 128), (64, 128), (128, 128) on four.  fp32 activations use bn = 64 and any
-// bm of 32, 64, 128 (N a multiple of 64).
+// bm of 32, 64, 128 (N a multiple of 64, bf16 output).
 struct GemmShape {
     int bm, bn, depth, epi;
-    int kg = 1;  // wave groups sharing K (ring kernels: 1 or 2)
+    // Wave groups sharing K, 1 or 2.  2: ring tiles (32, 64, 6), (64, 64, 4), (64, 128, 3)
+    // and (128, 128, 2), K a multiple of 128, no side job, no fp16 output.
+    int kg = 1;
 };
 // depth of the few-row kernel: bm 16, 32 or 48 covers all rows (M <= bm), bn
-// is not used; K of 128, 512 or 2048, bf16 activations (fp32 with K = 512).
+// is not used; bf16 activations with K = 2048 and any output but fp16, or K = 128
+// or 512 and bf16 output; fp32 activations with K = 512 and bf16 output.
 constexpr int kSkinny = -1;
 
 // The launch covers ceil(M / bm) * ceil(N / bn) tiles x batch, plus

@@ -885,23 +885,26 @@ __global__ __launch_bounds__(64 * kMhaWaves) void mha_prefill_kernel(const MhaAr
     }
 }
 
-template <int BM, int BN, int D, int KG>
-hipError_t launch_ring_kg(const GemmArgs &g, int epi, dim3 grid, hipStream_t s) {
-    if (epi == kStoreF16) gemm_ring_kernel<BM, BN, D, KG, kStoreF16><<<grid, 256 * KG, 0, s>>>(g);
-    else if (epi == kStoreBf16) gemm_ring_kernel<BM, BN, D, KG, kStoreBf16><<<grid, 256 * KG, 0, s>>>(g);
-    else if (epi == kStoreF32) gemm_ring_kernel<BM, BN, D, KG, kStoreF32><<<grid, 256 * KG, 0, s>>>(g);
-    else if (epi == kQkvSplit) gemm_ring_kernel<BM, BN, D, KG, kQkvSplit><<<grid, 256 * KG, 0, s>>>(g);
+template <int BM, int BN, int D>
+hipError_t launch_ring(const GemmArgs &g, const GemmShape &t, dim3 grid, hipStream_t s) {
+    if (t.kg != 1) return hipErrorInvalidValue;
+    if (t.epi == kStoreF16) gemm_ring_kernel<BM, BN, D, 1, kStoreF16><<<grid, 256, 0, s>>>(g);
+    else if (t.epi == kStoreBf16) gemm_ring_kernel<BM, BN, D, 1, kStoreBf16><<<grid, 256, 0, s>>>(g);
+    else if (t.epi == kStoreF32) gemm_ring_kernel<BM, BN, D, 1, kStoreF32><<<grid, 256, 0, s>>>(g);
+    else if (t.epi == kQkvSplit) gemm_ring_kernel<BM, BN, D, 1, kQkvSplit><<<grid, 256, 0, s>>>(g);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
+// The tiles that also exist with two wave groups sharing K (no side job, no fp16 output).
 template <int BM, int BN, int D>
-hipError_t launch_ring(const GemmArgs &g, const GemmShape &t, dim3 grid, hipStream_t s) {
-    if (t.kg == 2) {
-        if constexpr (2 * D * (BM + BN) * kBK * 2 <= 160 * 1024)
-            if (g.K % (2 * kBK) == 0 && g.rope_wgs == 0 && g.keys_wgs == 0) return launch_ring_kg<BM, BN, D, 2>(g, t.epi, grid, s);
-        return hipErrorInvalidValue;
-    }
-    return launch_ring_kg<BM, BN, D, 1>(g, t.epi, grid, s);
+hipError_t launch_ring_kg2(const GemmArgs &g, const GemmShape &t, dim3 grid, hipStream_t s) {
+    if (t.kg != 2) return launch_ring<BM, BN, D>(g, t, grid, s);
+    if (g.K % (2 * kBK) != 0 || g.rope_wgs != 0 || g.keys_wgs != 0) return hipErrorInvalidValue;
+    if (t.epi == kStoreBf16) gemm_ring_kernel<BM, BN, D, 2, kStoreBf16><<<grid, 512, 0, s>>>(g);
+    else if (t.epi == kStoreF32) gemm_ring_kernel<BM, BN, D, 2, kStoreF32><<<grid, 512, 0, s>>>(g);
+    else if (t.epi == kQkvSplit) gemm_ring_kernel<BM, BN, D, 2, kQkvSplit><<<grid, 512, 0, s>>>(g);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
 }
 
 // 256 x 256 tiles on eight waves (128 x 64 each), two 64 KB stages.
@@ -924,29 +927,24 @@ hipError_t launch_reg(const GemmArgs &g, int epi, dim3 grid, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int MB, int STEPS, int KS, bool A_F32>
-hipError_t launch_skinny(const GemmArgs &g, int epi, int batch, hipStream_t s) {
-    constexpr int cols = 16 * (8 / KS);
-    const dim3 grid((unsigned)((g.N + cols - 1) / cols + g.rope_wgs), 1, (unsigned)batch);
-    if (epi == kStoreBf16) gemm_skinny_kernel<MB, STEPS, KS, A_F32, kStoreBf16><<<grid, 512, 0, s>>>(g);
-    else if (epi == kStoreF32 && !A_F32) gemm_skinny_kernel<MB, STEPS, KS, false, kStoreF32><<<grid, 512, 0, s>>>(g);
-    else if (epi == kQkvSplit && !A_F32) gemm_skinny_kernel<MB, STEPS, KS, false, kQkvSplit><<<grid, 512, 0, s>>>(g);
+// K = 2048: the projections on the hidden rows and the output (every bf16-activation
+// epilogue); K = 512 and 128: value up-projection and query absorption (bf16 output).
+template <int MB>
+hipError_t launch_skinny(const GemmArgs &g, int epi, bool a_f32, int batch, hipStream_t s) {
+    const auto grid = [&](int cols) { return dim3((unsigned)((g.N + cols - 1) / cols + g.rope_wgs), 1, (unsigned)batch); };
+    if (g.K == 2048 && !a_f32 && epi == kQkvSplit) gemm_skinny_kernel<MB, 8, 8, false, kQkvSplit><<<grid(16), 512, 0, s>>>(g);
+    else if (g.K == 2048 && !a_f32 && epi == kStoreF32) gemm_skinny_kernel<MB, 8, 8, false, kStoreF32><<<grid(16), 512, 0, s>>>(g);
+    else if (g.K == 2048 && !a_f32 && epi == kStoreBf16) gemm_skinny_kernel<MB, 8, 8, false, kStoreBf16><<<grid(16), 512, 0, s>>>(g);
+    else if (g.K == 512 && a_f32 && epi == kStoreBf16) gemm_skinny_kernel<MB, 2, 8, true, kStoreBf16><<<grid(16), 512, 0, s>>>(g);
+    else if (g.K == 512 && !a_f32 && epi == kStoreBf16) gemm_skinny_kernel<MB, 2, 8, false, kStoreBf16><<<grid(16), 512, 0, s>>>(g);
+    else if (g.K == 128 && !a_f32 && epi == kStoreBf16) gemm_skinny_kernel<MB, 4, 1, false, kStoreBf16><<<grid(128), 512, 0, s>>>(g);
     else return hipErrorInvalidValue;
     return hipGetLastError();
-}
-
-template <int MB>
-hipError_t launch_skinny_k(const GemmArgs &g, int epi, bool a_f32, int batch, hipStream_t s) {
-    if (g.K == 2048 && !a_f32) return launch_skinny<MB, 8, 8, false>(g, epi, batch, s);
-    if (g.K == 512) return a_f32 ? launch_skinny<MB, 2, 8, true>(g, epi, batch, s) : launch_skinny<MB, 2, 8, false>(g, epi, batch, s);
-    if (g.K == 128 && !a_f32) return launch_skinny<MB, 4, 1, false>(g, epi, batch, s);
-    return hipErrorInvalidValue;
 }
 
 template <int BM>
 hipError_t launch_f32a(const GemmArgs &g, int epi, dim3 grid, hipStream_t s) {
     if (epi == kStoreBf16) gemm_f32a_kernel<BM, kStoreBf16><<<grid, 256, 0, s>>>(g);
-    else if (epi == kStoreF32) gemm_f32a_kernel<BM, kStoreF32><<<grid, 256, 0, s>>>(g);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
@@ -967,9 +965,9 @@ hipError_t launch_gemm(const GemmArgs &g, const GemmShape &t, bool a_f32, int ba
     if (t.depth == kSkinny) {
         if (g.a_bt != nullptr || g.keys_wgs != 0 || g.rope_wgs < 0 || g.M > t.bm) return hipErrorInvalidValue;
         switch (t.bm) {
-            case 16: return launch_skinny_k<1>(g, t.epi, a_f32, batch, s);
-            case 32: return launch_skinny_k<2>(g, t.epi, a_f32, batch, s);
-            case 48: return launch_skinny_k<3>(g, t.epi, a_f32, batch, s);
+            case 16: return launch_skinny<1>(g, t.epi, a_f32, batch, s);
+            case 32: return launch_skinny<2>(g, t.epi, a_f32, batch, s);
+            case 48: return launch_skinny<3>(g, t.epi, a_f32, batch, s);
             default: return hipErrorInvalidValue;
         }
     }
@@ -978,6 +976,7 @@ hipError_t launch_gemm(const GemmArgs &g, const GemmShape &t, bool a_f32, int ba
     if (tiles > 0x7FFFFFFF || g.rope_wgs < 0 || g.keys_wgs < 0 || (g.rope_wgs > 0 && g.keys_wgs > 0))
         return hipErrorInvalidValue;
     const dim3 grid((unsigned)tiles, 1, (unsigned)batch);
+    if (t.kg != 1 && (a_f32 || t.depth <= 0)) return hipErrorInvalidValue;
     if (a_f32 || t.depth == 0) {
         // gathered rows and fp16 output exist in the LDS-ring kernel only
         if (g.a_bt != nullptr || t.epi == kStoreF16) return hipErrorInvalidValue;
@@ -1001,12 +1000,12 @@ hipError_t launch_gemm(const GemmArgs &g, const GemmShape &t, bool a_f32, int ba
         case 128 * 1000 + 128 * 10 + 0: return launch_reg<128, 128, 2, 2>(g, t.epi, grid, s);
         case 64 * 1000 + 128 * 10 + 0: return launch_reg<64, 128, 2, 2>(g, t.epi, grid, s);
         case 32 * 1000 + 128 * 10 + 0: return launch_reg<32, 128, 2, 2>(g, t.epi, grid, s);
-        case 32 * 1000 + 64 * 10 + 6: return launch_ring<32, 64, 6>(g, t, grid, s);
-        case 64 * 1000 + 64 * 10 + 4: return launch_ring<64, 64, 4>(g, t, grid, s);
+        case 32 * 1000 + 64 * 10 + 6: return launch_ring_kg2<32, 64, 6>(g, t, grid, s);
+        case 64 * 1000 + 64 * 10 + 4: return launch_ring_kg2<64, 64, 4>(g, t, grid, s);
         case 128 * 1000 + 64 * 10 + 3: return launch_ring<128, 64, 3>(g, t, grid, s);
         case 32 * 1000 + 128 * 10 + 4: return launch_ring<32, 128, 4>(g, t, grid, s);
-        case 64 * 1000 + 128 * 10 + 3: return launch_ring<64, 128, 3>(g, t, grid, s);
-        case 128 * 1000 + 128 * 10 + 2: return launch_ring<128, 128, 2>(g, t, grid, s);
+        case 64 * 1000 + 128 * 10 + 3: return launch_ring_kg2<64, 128, 3>(g, t, grid, s);
+        case 128 * 1000 + 128 * 10 + 2: return launch_ring_kg2<128, 128, 2>(g, t, grid, s);
         case 128 * 1000 + 128 * 10 + 3: return launch_ring<128, 128, 3>(g, t, grid, s);
         default: return hipErrorInvalidValue;
     }

@@ -83,3 +83,37 @@ def test_all_three_forced(harness):
     calls = [(m, g, 128, 128, 3) for g in GEMMS for m in (1, 48, 300, 4160, 8000)]
     for c, got in zip(calls, picks(harness, calls)):
         assert got == (128, 64 if GEMMS[c[1]][4] else 128, 3, 1), c
+
+
+def kernel_of(gemm, shape):
+    """The kernel that computes `gemm` in `shape`, as the library's symbols name it."""
+    _, K, _, epi, f32, _ = GEMMS[gemm]
+    bm, bn, d, kg = shape
+    if d == -1:
+        steps, ks = {2048: (8, 8), 512: (2, 8), 128: (4, 1)}[K]
+        return f"gemm_skinny_kernel<{bm // 16}, {steps}, {ks}, {'true' if f32 else 'false'}, {epi}>"
+    if f32:
+        return f"gemm_f32a_kernel<{bm}, {epi}>"
+    if d == 0:
+        return f"gemm_reg_kernel<{bm}, {bn}, {4 if bm == 256 else 2}, {4 if bn == 256 else 2}, {epi}>"
+    return f"gemm_ring_kernel<{bm}, {bn}, {d}, {kg}, {epi}, 2, {4 if bn == 256 else 2}>"
+
+
+# every shape the tuning values may ask for (rows, columns, stages)
+FORCED = [(32, 64, 6), (64, 64, 4), (128, 64, 3), (32, 128, 4), (64, 128, 3), (128, 128, 2), (128, 128, 3),
+          (32, 128, 0), (64, 128, 0), (128, 128, 0), (128, 256, 0), (256, 128, 0)]
+
+
+def test_the_library_holds_the_kernels_that_are_chosen_and_no_others(harness):
+    """Kernel names from the symbol table of the library built here."""
+    lib = os.path.join(ROOT, "paper_2607_02043_amd", "libmlastep.so")
+    if not os.path.exists(lib) or shutil.which("nm") is None:
+        pytest.skip("library not built, or no nm")
+    symbols = subprocess.run(["nm", "-C", lib], capture_output=True, text=True, check=True).stdout
+    built = {line.split("__device_stub__")[1].split("(")[0] for line in symbols.splitlines() if "__device_stub__gemm_" in line}
+    calls = [(m, g, -1, -1, -1) for g in GEMMS for m in ROWS]
+    chosen = {kernel_of(c[1], p) for c, p in zip(calls, picks(harness, calls))}
+    forced = {kernel_of(g, (bm, bn, d, 1)) for g in GEMMS for bm, bn, d in FORCED
+              if not (GEMMS[g][3] == F16 and d == 0) and not (GEMMS[g][4] and bm > 128)}
+    assert chosen <= built, sorted(chosen - built)
+    assert built == chosen | forced, (sorted(built - chosen - forced), sorted(forced - built))
