@@ -209,10 +209,15 @@ __device__ __forceinline__ int item_tid() {
 
 // ------------------------------------------------------ work-item lookup
 // Items of one kind are numbered request by request; request r owns
-// count(r) consecutive items.  Every wavefront looks its item up by itself, 64
-// requests a step with the next 64 lengths already loading: no barrier and
-// no LDS exchange stands between the load of the lengths and the item's own
-// loads (a lookup is mostly the latency of that load).
+// count(r) consecutive items.  Every wavefront looks its item up by itself: no
+// barrier and no LDS exchange stands between the load of the lengths and the
+// item's own loads (a lookup is mostly the latency of that load).  It takes up
+// to 64 requests in one step, larger batches 256 a step (four lengths a lane,
+// their prefix sums independent) with the next 256 already
+// loading.  (64 a step with shuffles for the sums: 4000 rows of 16 to 256 keys
+// 307.9 -> 288.6 us, 1000 rows of 64 to 2048 keys 285.7 -> 281.1, 4 rows 18.8 ->
+// 18.2; the lane addresses of the shuffles were also held across the items, which
+// cost the chunk tiles registers: 20 spilled, now none.)
 struct ReqLens {
     const int32_t *cu_q;
     const int32_t *prefix;
@@ -234,39 +239,61 @@ __device__ __forceinline__ LenRow load_lens(const int32_t *cu_q, const int32_t *
     return l;
 }
 
-// Inclusive prefix sum over the lanes of a wavefront.
-__device__ __forceinline__ int wave_scan(int v, int lane) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int t = __shfl_up(v, d, 64);
-        if (lane >= d) v += t;
-    }
+// Inclusive prefix sum over the lanes of a wavefront, all of them active: inside
+// rows of 16 lanes by shifts, then the last lane of row 0 (2) added to row 1
+// (3) and lane 31 to rows 2 and 3, all in the vector unit (DPP).
+__device__ __forceinline__ int wave_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
     return v;
+}
+
+constexpr int kLookupQ = 4;  // lengths a lane and step of a lookup over more than 64 requests
+
+template <int Q, typename CountFn>
+__device__ __forceinline__ bool locate_in(int target, int num_reqs, const ReqLens &rl, CountFn count, Located &loc) {
+    const int lane = item_tid() & 63;
+    const auto req = [&](int i) { return rl.rev ? num_reqs - 1 - i : i; };
+    LenRow cur[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) cur[q] = load_lens(rl.cu_q, rl.prefix, req(64 * q + lane), num_reqs);
+    int running = 0;
+    for (int base = 0; base < num_reqs; base += 64 * Q) {
+        LenRow nxt[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) nxt[q] = load_lens(rl.cu_q, rl.prefix, req(base + 64 * (Q + q) + lane), num_reqs);
+        int cnt[Q], inc[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            cnt[q] = base + 64 * q + lane < num_reqs ? count(cur[q].p, cur[q].next - cur[q].row0) : 0;
+            inc[q] = wave_scan(cnt[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int end = running + inc[q], first = end - cnt[q];
+            const uint64_t hit = __builtin_amdgcn_ballot_w64(cnt[q] > 0 && target >= first && target < end);
+            if (hit != 0) {
+                const int l = __builtin_ctzll(hit);
+                loc = Located{req(base + 64 * q + l), target - __builtin_amdgcn_readlane(first, l),
+                              __builtin_amdgcn_readlane(cur[q].p, l), __builtin_amdgcn_readlane(cur[q].row0, l),
+                              __builtin_amdgcn_readlane(cur[q].next - cur[q].row0, l)};
+                return true;
+            }
+            running = __builtin_amdgcn_readlane(end, 63);
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) cur[q] = nxt[q];
+    }
+    return false;
 }
 
 template <typename CountFn>
 __device__ bool locate_item(int target, int num_reqs, const ReqLens &rl, CountFn count, Located &loc) {
-    const int lane = item_tid() & 63;
-    const auto req = [&](int base) { return rl.rev ? num_reqs - 1 - (base + lane) : base + lane; };
-    int running = 0;
-    LenRow cur = load_lens(rl.cu_q, rl.prefix, req(0), num_reqs);
-    for (int base = 0; base < num_reqs; base += 64) {
-        const LenRow nxt = load_lens(rl.cu_q, rl.prefix, req(base + 64), num_reqs);
-        const int r = req(base), c = cur.next - cur.row0;
-        const int cnt = (unsigned)r < (unsigned)num_reqs ? count(cur.p, c) : 0;
-        const int inc = running + wave_scan(cnt, lane);
-        const uint64_t hit = __builtin_amdgcn_ballot_w64(cnt > 0 && target >= inc - cnt && target < inc);
-        if (hit != 0) {
-            const int l = __builtin_ctzll(hit);
-            loc = Located{__builtin_amdgcn_readlane(r, l), target - __builtin_amdgcn_readlane(inc - cnt, l),
-                          __builtin_amdgcn_readlane(cur.p, l), __builtin_amdgcn_readlane(cur.row0, l),
-                          __builtin_amdgcn_readlane(c, l)};
-            return true;
-        }
-        running = __builtin_amdgcn_readlane(inc, 63);
-        cur = nxt;
-    }
-    return false;
+    return num_reqs <= 64 ? locate_in<1>(target, num_reqs, rl, count, loc) : locate_in<kLookupQ>(target, num_reqs, rl, count, loc);
 }
 
 struct ChunkCount {
@@ -528,34 +555,51 @@ __device__ __forceinline__ int dec_tiles(int p, int c) { return c == 1 ? ceil_di
 
 // Segments (request order) of the decode tile range [R0, R1), with the page
 // window each needs; returns their count.  Every wavefront of a group finds
-// them by itself and `writer` stores them.
-__device__ int find_unit(const AttnArgs &a, int R0, int R1, DecSeg *s_seg, bool writer) {
+// them by itself (as a lookup does) and `writer` stores them.
+template <int Q>
+__device__ __forceinline__ int find_unit_in(const AttnArgs &a, int R0, int R1, DecSeg *s_seg, bool writer) {
     const int lane = item_tid() & 63;
     int running = 0, nseg = 0, pages = 0;
-    LenRow cur = load_lens(a.cu_q, a.prefix, lane, a.num_reqs);
-    for (int base = 0; base < a.num_reqs && running < R1; base += 64) {
-        const LenRow nxt = load_lens(a.cu_q, a.prefix, base + 64 + lane, a.num_reqs);
-        // rows outside [0, T) only arise from device lengths that disagree with the host's
-        const bool row_ok = base + lane < a.num_reqs && cur.p >= 0 && cur.row0 >= 0 && cur.row0 < a.num_rows;
-        const int nt = row_ok ? dec_tiles(cur.p, cur.next - cur.row0) : 0;
-        const int inc = running + wave_scan(nt, lane);
-        const int T = inc - nt;
-        const bool ov = nt > 0 && T < R1 && inc > R0;
-        const uint64_t m = __builtin_amdgcn_ballot_w64(ov);
-        if (m != 0) {
-            const int t0 = max(R0 - T, 0), t1 = min(R1 - T, nt);
-            const int lp0 = (t0 * kDecKeys) >> a.log2_page;
-            const int np = ov ? ((min(t1 * kDecKeys, cur.p + 1) - 1) >> a.log2_page) - lp0 + 1 : 0;
-            const int pend = pages + wave_scan(np, lane);
-            const int j = nseg + __builtin_popcountll(m & ((1ull << lane) - 1));
-            if (ov && writer && j < kMaxSeg) s_seg[j] = DecSeg{base + lane, cur.p, cur.row0, t0, t1, pend - np, lp0};
-            nseg += __builtin_popcountll(m);
-            pages = __builtin_amdgcn_readlane(pend, 63);
+    LenRow cur[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) cur[q] = load_lens(a.cu_q, a.prefix, 64 * q + lane, a.num_reqs);
+    for (int base = 0; base < a.num_reqs && running < R1; base += 64 * Q) {
+        LenRow nxt[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) nxt[q] = load_lens(a.cu_q, a.prefix, base + 64 * (Q + q) + lane, a.num_reqs);
+        int nt[Q], inc[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            // rows outside [0, T) only arise from device lengths that disagree with the host's
+            const bool row_ok = base + 64 * q + lane < a.num_reqs && cur[q].p >= 0 && cur[q].row0 >= 0 && cur[q].row0 < a.num_rows;
+            nt[q] = row_ok ? dec_tiles(cur[q].p, cur[q].next - cur[q].row0) : 0;
+            inc[q] = wave_scan(nt[q]);
         }
-        running = __builtin_amdgcn_readlane(inc, 63);
-        cur = nxt;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int end = running + inc[q], T = end - nt[q];
+            const bool ov = nt[q] > 0 && T < R1 && end > R0;
+            const uint64_t m = __builtin_amdgcn_ballot_w64(ov);
+            if (m != 0) {
+                const int t0 = max(R0 - T, 0), t1 = min(R1 - T, nt[q]);
+                const int lp0 = (t0 * kDecKeys) >> a.log2_page;
+                const int np = ov ? ((min(t1 * kDecKeys, cur[q].p + 1) - 1) >> a.log2_page) - lp0 + 1 : 0;
+                const int pend = pages + wave_scan(np);
+                const int j = nseg + __builtin_popcountll(m & ((1ull << lane) - 1));
+                if (ov && writer && j < kMaxSeg)
+                    s_seg[j] = DecSeg{base + 64 * q + lane, cur[q].p, cur[q].row0, t0, t1, pend - np, lp0};
+                nseg += __builtin_popcountll(m);
+                pages = __builtin_amdgcn_readlane(pend, 63);
+            }
+            running = __builtin_amdgcn_readlane(end, 63);
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) cur[q] = nxt[q];
     }
     return min(nseg, kMaxSeg);
+}
+__device__ int find_unit(const AttnArgs &a, int R0, int R1, DecSeg *s_seg, bool writer) {
+    return a.num_reqs <= 64 ? find_unit_in<1>(a, R0, R1, s_seg, writer) : find_unit_in<kLookupQ>(a, R0, R1, s_seg, writer);
 }
 
 // Unit cursor of a group's stream: segment j, tile t (t < 0: the query block).
