@@ -126,8 +126,10 @@ int check_batch(const mla_batch *b, Shape *sh) {
 
 struct Plan {
     int ks_chunk = 0, n_chunk_items = 0;
-    int n_dec_units = 0, dec_unit_tiles = 0, dec_total_tiles = 0, grid = 0, merge_hsplit = 1;
+    int n_dec_units = 0, dec_unit_tiles = 0, dec_total_tiles = 0, grid = 0;
     int dec_first_wgs = 0;  // workgroups that take decode items before chunk items
+    int n_split_rows = 0;   // decode rows cut across units
+    bool merge_many = false;  // one of them into more than mla::kMergeFewParts parts
     bool chunk_split = false, dec_split = false, chunk_rev = false;
     size_t off_chunk_o = 0, off_chunk_ml = 0, off_dec_o = 0, off_dec_ml = 0, bytes = 0;
     // what a warm start compares: the work of the batch the plan was made for
@@ -751,14 +753,12 @@ int make_plan_uncached(const mla_batch *b, const Shape &sh, int ncu, mla::ChunkR
         const long long first = forced_first >= 0 ? forced_first : warm != nullptr ? warm->dec_first_wgs : dec_first;
         pl->dec_first_wgs = nci > 0 && dec_total > 0 ? (int)std::min<long long>(first, pl->grid) : 0;
     }
-    long long max_parts = 1;
     for (const DecReq &d : dec) {
         const long long parts = (d.first_tile + d.tiles - 1) / U - d.first_tile / U + 1;
-        if (parts > 1) pl->dec_split = true;
-        max_parts = std::max(max_parts, parts);
+        pl->n_split_rows += parts > 1;
+        pl->merge_many |= parts > mla::kMergeFewParts;
     }
-    // a row merged from many parts is spread over several workgroups
-    pl->merge_hsplit = max_parts > 16 ? 8 : max_parts > 4 ? 4 : 1;
+    pl->dec_split = pl->n_split_rows > 0;
     size_t off = kCounterBytes;
     if (pl->chunk_split) {
         pl->off_chunk_o = off;
@@ -777,9 +777,9 @@ int make_plan_uncached(const mla_batch *b, const Shape &sh, int ncu, mla::ChunkR
     if (log_plan)
         std::fprintf(stderr,
                      "[mla plan] R=%d CUs=%d chunk items=%d (ks=%d keys, split=%d, rev=%d) decode units=%d x %d "
-                     "tiles (total %lld, split=%d, merge x%d) grid=%d decode-first=%d workspace=%zu B%s\n",
+                     "tiles (total %lld, split rows=%d, many parts=%d) grid=%d decode-first=%d workspace=%zu B%s\n",
                      sh.R, ncu, pl->n_chunk_items, pl->ks_chunk, (int)pl->chunk_split, (int)pl->chunk_rev,
-                     pl->n_dec_units, pl->dec_unit_tiles, dec_total, (int)pl->dec_split, pl->merge_hsplit, pl->grid,
+                     pl->n_dec_units, pl->dec_unit_tiles, dec_total, pl->n_split_rows, (int)pl->merge_many, pl->grid,
                      pl->dec_first_wgs, pl->bytes, pl->warm ? " (warm)" : "");
     return MLA_OK;
 }
@@ -1067,7 +1067,8 @@ int attend(const mla_batch *batch, const uint16_t *q, const uint16_t *new_latent
     a.dec_unit_tiles = pl.dec_unit_tiles;
     a.grid = pl.grid;
     a.dec_first_wgs = pl.dec_first_wgs;
-    a.merge_hsplit = pl.merge_hsplit;
+    a.n_split_rows = pl.n_split_rows;
+    a.merge_many = pl.merge_many ? 1 : 0;
     a.dec_total_tiles = pl.dec_total_tiles;
     a.out_bf16 = out_dtype == MLA_OUT_BF16 ? 1 : 0;
     a.spin_limit = debug_value(MLA_DEBUG_SPIN_LIMIT).load(std::memory_order_relaxed);

@@ -57,7 +57,8 @@ struct AttnArgs {
     int32_t dec_total_tiles;
     int32_t grid;              // persistent workgroups of the attention launch
     int32_t dec_first_wgs;     // workgroups 0 .. dec_first_wgs - 1 take decode items before chunk items
-    int32_t merge_hsplit;      // size class of the most split decode row: 1 (at most 4 parts), 4 (at most 16) or 8
+    int32_t n_split_rows;      // decode rows cut across units: the merge launches workgroups for these alone
+    int32_t merge_many;        // 1: some decode row is cut into more than kMergeFewParts parts
     int32_t out_bf16;
     int32_t spin_limit;        // sleeps of a bounded wait before it gives up (kSpinLimit)
     ChunkRoute route;          // chunk requests it sends to the multi-head path are left out of this launch
@@ -78,6 +79,11 @@ __host__ __device__ inline int first_item(int n_chunk, int n_dec, int D, int G, 
     const int k = b - D;
     return k < n_chunk ? k : n_chunk + (D < n_dec ? D : n_dec) + (k - n_chunk);
 }
+
+// Merge workgroups of a split decode row: of four heads each, or of one head
+// (four wavefronts on every fourth part) when rows have many parts.
+constexpr int kMergeFewParts = 16;
+__host__ __device__ inline int merge_wgs(const AttnArgs &a) { return a.merge_many ? kHeads : kHeads / 4; }
 
 struct AppendArgs {
     const uint16_t *src;

@@ -6,7 +6,7 @@
 // (PLAN_ROUTE, PLAN_CHUNK_KEYS, PLAN_DEC_UNIT, PLAN_DEC_FIRST and PLAN_SERVING in the
 // environment: see main)
 // Output, one line per batch:
-//   ok ks n_chunk_items n_dec_items unit_tiles dec_total grid merge_hsplit chunk_split dec_split bytes
+//   ok ks n_chunk_items n_dec_items unit_tiles dec_total grid merge_many chunk_split split_rows bytes
 //      off_chunk_o off_chunk_ml off_dec_o off_dec_ml plan_us warm est_us dec_first_wgs
 // or "err <status> <message>".
 // A line "ws <bytes> page_size R q_0 p_0 ..." instead calls the real
@@ -182,8 +182,8 @@ int main() {
             continue;
         }
         std::cout << "ok " << pl.ks_chunk << " " << pl.n_chunk_items << " " << pl.n_dec_units << " "
-                  << pl.dec_unit_tiles << " " << pl.dec_total_tiles << " " << pl.grid << " " << pl.merge_hsplit << " "
-                  << (int)pl.chunk_split << " " << (int)pl.dec_split << " " << pl.bytes << " " << pl.off_chunk_o << " "
+                  << pl.dec_unit_tiles << " " << pl.dec_total_tiles << " " << pl.grid << " " << (int)pl.merge_many << " "
+                  << (int)pl.chunk_split << " " << pl.n_split_rows << " " << pl.bytes << " " << pl.off_chunk_o << " "
                   << pl.off_chunk_ml << " " << pl.off_dec_o << " " << pl.off_dec_ml << " " << us << " "
                   << (int)pl.warm << " " << pl.est_us << " " << pl.dec_first_wgs << "\n";
     }

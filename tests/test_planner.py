@@ -53,8 +53,8 @@ def plan(exe, batches, route=None, chunk_keys=None, dec_unit=None, dec_first=Non
         if f[0] == "err":
             res.append(("err", int(f[1]), " ".join(f[2:])))
             continue
-        keys = ["ks", "n_chunk_items", "n_dec_items", "U", "dec_total", "grid", "hsplit", "chunk_split",
-                "dec_split", "bytes", "off_co", "off_cml", "off_do", "off_dml"]
+        keys = ["ks", "n_chunk_items", "n_dec_items", "U", "dec_total", "grid", "merge_many", "chunk_split",
+                "split_rows", "bytes", "off_co", "off_cml", "off_do", "off_dml"]
         d = {k: int(v) for k, v in zip(keys, f[1:15])}
         d["us"], d["est"], d["first"] = float(f[15]), float(f[17]), int(f[18])
         res.append(d)
@@ -122,12 +122,13 @@ def check_plan(batch, d, route=None):
         assert d["n_dec_items"] == -(-units // 2)
         seg, pages = unit_limits(dec, U, P)
         assert seg <= MAX_SEG and pages <= PAGE_WINDOW
-        parts = max((f + t - 1) // U - f // U + 1 for f, t, _ in dec)
-        assert d["dec_split"] == int(parts > 1)
-        assert d["hsplit"] == (8 if parts > 16 else 4 if parts > 4 else 1)
+        parts = [(f + t - 1) // U - f // U + 1 for f, t, _ in dec]
+        # the merge is launched for the rows cut across units, whatever the batch
+        assert d["split_rows"] == sum(n > 1 for n in parts)
+        assert d["merge_many"] == int(max(parts) > 16)
     else:
         units = 0
-        assert d["n_dec_items"] == 0 and d["dec_split"] == 0
+        assert d["n_dec_items"] == 0 and d["split_rows"] == 0
     assert 1 <= d["grid"] <= ncu and d["grid"] <= d["n_chunk_items"] + d["n_dec_items"]
     # decode-first workgroups: only with both kinds of work, at most the launch
     assert 0 <= d["first"] <= d["grid"]
@@ -141,7 +142,7 @@ def check_plan(batch, d, route=None):
         off = align(off + d["n_chunk_items"] * BLOCK_TOKENS * PARTIAL_FLOATS * 4)
         assert d["off_cml"] == off
         off = align(off + d["n_chunk_items"] * BLOCK_TOKENS * PARTIAL_STATS * 4)
-    if d["dec_split"]:
+    if d["split_rows"]:
         assert d["off_do"] == off
         off = align(off + 2 * units * PARTIAL_FLOATS * 4)
         assert d["off_dml"] == off
@@ -295,8 +296,8 @@ def _serving_plans(harness, batches):
     for line in out.splitlines():
         f = line.split()
         assert f[0] == "ok", line
-        keys = ["ks", "n_chunk_items", "n_dec_items", "U", "dec_total", "grid", "hsplit", "chunk_split",
-                "dec_split", "bytes", "off_co", "off_cml", "off_do", "off_dml"]
+        keys = ["ks", "n_chunk_items", "n_dec_items", "U", "dec_total", "grid", "merge_many", "chunk_split",
+                "split_rows", "bytes", "off_co", "off_cml", "off_do", "off_dml"]
         d = {k: int(v) for k, v in zip(keys, f[1:15])}
         d["us"], d["warm"], d["first"] = float(f[15]), int(f[16]), int(f[18])
         res.append(d)
