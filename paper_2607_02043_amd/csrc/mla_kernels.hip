@@ -150,7 +150,6 @@ __device__ __forceinline__ void lds_dma16(const void *gsrc, uint32_t lds_base) {
 }
 
 __device__ __forceinline__ void wait_dma_all() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-__device__ __forceinline__ void wait_dma_keep9() { asm volatile("s_waitcnt vmcnt(9)" ::: "memory"); }
 
 __device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
@@ -254,6 +253,11 @@ __device__ __forceinline__ int wave_scan(int v) {
 
 constexpr int kLookupQ = 4;  // lengths a lane and step of a lookup over more than 64 requests
 
+// End of a lookup: its loads, which nothing reads any more, count as landed.
+// (Left in flight as far as the compiler knows, it waits for them where it next
+// writes their registers, and there for every load issued in between.)
+__device__ __forceinline__ void end_lookup() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0), the others left alone
+
 template <int Q, typename CountFn>
 __device__ __forceinline__ bool locate_in(int target, int num_reqs, const ReqLens &rl, CountFn count, Located &loc) {
     const int lane = item_tid() & 63;
@@ -264,8 +268,10 @@ __device__ __forceinline__ bool locate_in(int target, int num_reqs, const ReqLen
     int running = 0;
     for (int base = 0; base < num_reqs; base += 64 * Q) {
         LenRow nxt[Q];
+        if constexpr (Q > 1) {
 #pragma unroll
-        for (int q = 0; q < Q; ++q) nxt[q] = load_lens(rl.cu_q, rl.prefix, req(base + 64 * (Q + q) + lane), num_reqs);
+            for (int q = 0; q < Q; ++q) nxt[q] = load_lens(rl.cu_q, rl.prefix, req(base + 64 * (Q + q) + lane), num_reqs);
+        }
         int cnt[Q], inc[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
@@ -285,6 +291,7 @@ __device__ __forceinline__ bool locate_in(int target, int num_reqs, const ReqLen
             }
             running = __builtin_amdgcn_readlane(end, 63);
         }
+        if constexpr (Q == 1) break;  // at most 64 requests
 #pragma unroll
         for (int q = 0; q < Q; ++q) cur[q] = nxt[q];
     }
@@ -293,7 +300,9 @@ __device__ __forceinline__ bool locate_in(int target, int num_reqs, const ReqLen
 
 template <typename CountFn>
 __device__ bool locate_item(int target, int num_reqs, const ReqLens &rl, CountFn count, Located &loc) {
-    return num_reqs <= 64 ? locate_in<1>(target, num_reqs, rl, count, loc) : locate_in<kLookupQ>(target, num_reqs, rl, count, loc);
+    const bool found = num_reqs <= 64 ? locate_in<1>(target, num_reqs, rl, count, loc) : locate_in<kLookupQ>(target, num_reqs, rl, count, loc);
+    end_lookup();
+    return found;
 }
 
 struct ChunkCount {
@@ -565,8 +574,10 @@ __device__ __forceinline__ int find_unit_in(const AttnArgs &a, int R0, int R1, D
     for (int q = 0; q < Q; ++q) cur[q] = load_lens(a.cu_q, a.prefix, 64 * q + lane, a.num_reqs);
     for (int base = 0; base < a.num_reqs && running < R1; base += 64 * Q) {
         LenRow nxt[Q];
+        if constexpr (Q > 1) {
 #pragma unroll
-        for (int q = 0; q < Q; ++q) nxt[q] = load_lens(a.cu_q, a.prefix, base + 64 * (Q + q) + lane, a.num_reqs);
+            for (int q = 0; q < Q; ++q) nxt[q] = load_lens(a.cu_q, a.prefix, base + 64 * (Q + q) + lane, a.num_reqs);
+        }
         int nt[Q], inc[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
@@ -593,13 +604,16 @@ __device__ __forceinline__ int find_unit_in(const AttnArgs &a, int R0, int R1, D
             }
             running = __builtin_amdgcn_readlane(end, 63);
         }
+        if constexpr (Q == 1) break;  // at most 64 requests
 #pragma unroll
         for (int q = 0; q < Q; ++q) cur[q] = nxt[q];
     }
     return min(nseg, kMaxSeg);
 }
 __device__ int find_unit(const AttnArgs &a, int R0, int R1, DecSeg *s_seg, bool writer) {
-    return a.num_reqs <= 64 ? find_unit_in<1>(a, R0, R1, s_seg, writer) : find_unit_in<kLookupQ>(a, R0, R1, s_seg, writer);
+    const int nseg = a.num_reqs <= 64 ? find_unit_in<1>(a, R0, R1, s_seg, writer) : find_unit_in<kLookupQ>(a, R0, R1, s_seg, writer);
+    end_lookup();
+    return nseg;
 }
 
 // Unit cursor of a group's stream: segment j, tile t (t < 0: the query block).
@@ -918,8 +932,10 @@ __device__ __forceinline__ bool find_split_in(const AttnArgs &a, int k, SplitRow
     for (int q = 0; q < Q; ++q) cur[q] = load_lens(a.cu_q, a.prefix, 64 * q + lane, a.num_reqs);
     for (int base = 0; base < a.num_reqs; base += 64 * Q) {
         LenRow nxt[Q];
+        if constexpr (Q > 1) {
 #pragma unroll
-        for (int q = 0; q < Q; ++q) nxt[q] = load_lens(a.cu_q, a.prefix, base + 64 * (Q + q) + lane, a.num_reqs);
+            for (int q = 0; q < Q; ++q) nxt[q] = load_lens(a.cu_q, a.prefix, base + 64 * (Q + q) + lane, a.num_reqs);
+        }
         int nt[Q], inc[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
@@ -943,6 +959,7 @@ __device__ __forceinline__ bool find_split_in(const AttnArgs &a, int k, SplitRow
             splits += __builtin_popcountll(m);
             tiles = __builtin_amdgcn_readlane(T + nt[q], 63);
         }
+        if constexpr (Q == 1) break;  // at most 64 requests
 #pragma unroll
         for (int q = 0; q < Q; ++q) cur[q] = nxt[q];
     }
@@ -954,6 +971,7 @@ template <bool MANY>
 __device__ void decode_merge(const AttnArgs &a, int k, int part, float *s_o, float *s_ml) {
     SplitRow sr;
     if (!(a.num_reqs <= 64 ? find_split_in<1>(a, k, sr) : find_split_in<kLookupQ>(a, k, sr))) return;
+    end_lookup();
     const int S = a.dec_unit_tiles, T = sr.T, row = sr.row;
     const int w0 = T / S, w1 = (T + sr.nt - 1) / S;
     if (T + sr.nt > a.dec_total_tiles) return;  // device lengths beyond the host's: no such unit
@@ -1133,8 +1151,8 @@ __device__ bool chunk_item(const AttnArgs &a, int item, char *smem, int *s_pages
     for (int db = 0; db < 4; ++db)
         vt_off[db] = 4096 * wv + 128 * tr_key + 16 * ((2 * db + ((lane >> 1) & 1)) ^ (tr_key & 7)) + 8 * (lane & 1);
 
-    // DMA of tile t into its ring slot, issued by waves 4..7 only (nine rounds
-    // each: round i = (wv - 4) + 4 j).  Issuing stalls a wave for a while; the
+    // DMA of tile t into its ring slot, issued by waves 4..7 only (the first tile by
+    // waves 0..3; nine rounds each: round i = (wv & 3) + 4 j).  Issuing stalls a wave for a while; the
     // other wave of the same SIMD meanwhile runs ahead on its matrix work, so
     // the two wavefronts of a SIMD drift apart by about that much and the
     // softmax of one overlaps the products of the other.  A full tile inside
@@ -1150,7 +1168,6 @@ __device__ bool chunk_item(const AttnArgs &a, int item, char *smem, int *s_pages
         return s_pages[min(((it.k0 + t * kChunkKeys) >> a.log2_page) - lp0, kPageWindow - 1)];
     };
     auto issue = [&](int t, int slot, int page) {
-        if (!dma_wave) return;
         const int kbase = it.k0 + t * kChunkKeys;
         const uint32_t dst = ring + slot * kChunkTileBytes + dw * 1024;  // round r = dw + 4 r'
         if (in_page && kbase + kChunkKeys <= cached_end) {
@@ -1289,16 +1306,24 @@ __device__ bool chunk_item(const AttnArgs &a, int item, char *smem, int *s_pages
     if (exact) m_ref = s_mx[wv * kHeads + hd];
     if (tid == 0) *s_abort = 0;
     lds_barrier();  // page window and abort flag ready; the ring is idle
-    for (int t = 0; t < 2 && t < ntiles; ++t) issue(t, t, page_of(t));
+    // Waves 0..3 issue tile 0 at once, beside their queries; waves 4..7 issue
+    // tile 1 when theirs have landed.  The compiler does not count the
+    // DMAs, so a wait of its own for a query load would wait for every DMA the
+    // wave has issued since: this way it only waits for tile 0, which the barrier
+    // waits for anyway, and tile 1 stays in flight across it.  (Both tiles from
+    // waves 4..7, the queries awaited behind them: 5 + 32 rows 22.6 -> 22.3 us, 32 +
+    // 512 rows 41.0 -> 40.4, ragged chunks in two calls 85.0 -> 84.1.)
+    if (!dma_wave) issue(0, 0, page_of(0));
+#pragma unroll
+    for (int s = 0; s < kQRegSteps; ++s) asm volatile("" : "+v"(qreg[s]));
+#pragma unroll
+    for (int s = 0; s < kQSteps - kQRegSteps; ++s) asm volatile("" : "+v"(qr[s]));
+    wait_dma_all();
+    if (dma_wave && ntiles > 1) issue(1, 1, page_of(1));
 #pragma unroll
     for (int s = 0; s < kQSteps - kQRegSteps; ++s)
         *reinterpret_cast<u32x4 *>(s_q + ((s * kCT + wv) * 64 + lane) * 16) = qr[s];
-    // queries and tile 0 landed (tile 1's nine rounds may still be in flight)
-    if (ntiles == 1 || !dma_wave)
-        wait_dma_all();
-    else
-        wait_dma_keep9();
-    __syncthreads();
+    __syncthreads();  // queries and tile 0 landed
 #pragma unroll
     for (int tb = 0; tb < kCT; ++tb)
 #pragma unroll
@@ -1329,7 +1354,7 @@ __device__ bool chunk_item(const AttnArgs &a, int item, char *smem, int *s_pages
         TRACE_TILE(t, 12);
         const int slot1 = slot == kChunkRing - 1 ? 0 : slot + 1;
         const int slot2 = slot1 == kChunkRing - 1 ? 0 : slot1 + 1;
-        if (t + 2 < ntiles) issue(t + 2, slot2, next_page);
+        if (dma_wave && t + 2 < ntiles) issue(t + 2, slot2, next_page);
         TRACE_TILE(t, 14);
         pv(t & 1);
         TRACE_TILE(t, 15);
