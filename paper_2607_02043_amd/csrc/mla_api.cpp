@@ -130,6 +130,7 @@ struct Plan {
     int dec_first_wgs = 0;  // workgroups that take decode items before chunk items
     int n_split_rows = 0;   // decode rows cut across units
     bool merge_many = false;  // one of them into more than mla::kMergeFewParts parts
+    int n_split_chunk_rows = 0, chunk_merge_wgs = 1;  // rows of the chunk requests cut into key ranges, merge workgroups each
     bool chunk_split = false, dec_split = false, chunk_rev = false;
     size_t off_chunk_o = 0, off_chunk_ml = 0, off_dec_o = 0, off_dec_ml = 0, bytes = 0;
     // what a warm start compares: the work of the batch the plan was made for
@@ -729,12 +730,15 @@ int make_plan_uncached(const mla_batch *b, const Shape &sh, int ncu, mla::ChunkR
     }
     const long long U = dec_total > 0 ? U_best : 0;
     const long long n_units = dec_total > 0 ? ceil_div_ll(dec_total, U) : 0;
-    long long nci = 0;
+    long long nci = 0, chunk_parts = 1;
     for (const auto &pc : chunks) {
-        const long long p = pc.first, c = pc.second;
-        nci += ceil_div_ll(c, BM) * ceil_div_ll(p + c, ks_best);
-        if (ceil_div_ll(p + c, ks_best) > 1) pl->chunk_split = true;
+        const long long p = pc.first, c = pc.second, parts = ceil_div_ll(p + c, ks_best);
+        nci += ceil_div_ll(c, BM) * parts;
+        if (parts > 1) pl->n_split_chunk_rows += (int)c;
+        chunk_parts = std::max(chunk_parts, parts);
     }
+    pl->chunk_split = pl->n_split_chunk_rows > 0;
+    pl->chunk_merge_wgs = mla::chunk_merge_wgs(chunk_parts);
     if (nci > (1LL << 27)) return fail(MLA_ERR_INVALID_ARG, "step needs too many work items");
     pl->chunk_rev = rev;
     pl->chunk_pairs = chunk_pairs;
@@ -776,9 +780,9 @@ int make_plan_uncached(const mla_batch *b, const Shape &sh, int ncu, mla::ChunkR
     static const bool log_plan = std::getenv("MLA_PLAN_LOG") != nullptr;
     if (log_plan)
         std::fprintf(stderr,
-                     "[mla plan] R=%d CUs=%d chunk items=%d (ks=%d keys, split=%d, rev=%d) decode units=%d x %d "
+                     "[mla plan] R=%d CUs=%d chunk items=%d (ks=%d keys, split rows=%d, rev=%d) decode units=%d x %d "
                      "tiles (total %lld, split rows=%d, many parts=%d) grid=%d decode-first=%d workspace=%zu B%s\n",
-                     sh.R, ncu, pl->n_chunk_items, pl->ks_chunk, (int)pl->chunk_split, (int)pl->chunk_rev,
+                     sh.R, ncu, pl->n_chunk_items, pl->ks_chunk, pl->n_split_chunk_rows, (int)pl->chunk_rev,
                      pl->n_dec_units, pl->dec_unit_tiles, dec_total, pl->n_split_rows, (int)pl->merge_many, pl->grid,
                      pl->dec_first_wgs, pl->bytes, pl->warm ? " (warm)" : "");
     return MLA_OK;
@@ -1069,6 +1073,8 @@ int attend(const mla_batch *batch, const uint16_t *q, const uint16_t *new_latent
     a.dec_first_wgs = pl.dec_first_wgs;
     a.n_split_rows = pl.n_split_rows;
     a.merge_many = pl.merge_many ? 1 : 0;
+    a.n_split_chunk_rows = pl.n_split_chunk_rows;
+    a.chunk_merge_wgs = pl.chunk_merge_wgs;
     a.dec_total_tiles = pl.dec_total_tiles;
     a.out_bf16 = out_dtype == MLA_OUT_BF16 ? 1 : 0;
     a.spin_limit = debug_value(MLA_DEBUG_SPIN_LIMIT).load(std::memory_order_relaxed);

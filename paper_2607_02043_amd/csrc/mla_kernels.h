@@ -59,6 +59,8 @@ struct AttnArgs {
     int32_t dec_first_wgs;     // workgroups 0 .. dec_first_wgs - 1 take decode items before chunk items
     int32_t n_split_rows;      // decode rows cut across units: the merge launches workgroups for these alone
     int32_t merge_many;        // 1: some decode row is cut into more than kMergeFewParts parts
+    int32_t n_split_chunk_rows;  // rows of the chunk requests whose keys are cut into ranges
+    int32_t chunk_merge_wgs;     // merge workgroups of each of them (chunk_merge_wgs())
     int32_t out_bf16;
     int32_t spin_limit;        // sleeps of a bounded wait before it gives up (kSpinLimit)
     ChunkRoute route;          // chunk requests it sends to the multi-head path are left out of this launch
@@ -84,6 +86,13 @@ __host__ __device__ inline int first_item(int n_chunk, int n_dec, int D, int G, 
 // (four wavefronts on every fourth part) when rows have many parts.
 constexpr int kMergeFewParts = 16;
 __host__ __device__ inline int merge_wgs(const AttnArgs &a) { return a.merge_many ? kHeads : kHeads / 4; }
+// Merge workgroups of a split chunk row of at most `parts` parts: one for the
+// whole row (four heads a wavefront, one after the other), or as a decode row
+// where the chain of its loads would be long.
+constexpr int kChunkMergeFewParts = 4;
+inline int chunk_merge_wgs(long long parts) {
+    return parts > kMergeFewParts ? kHeads : parts > kChunkMergeFewParts ? kHeads / 4 : 1;
+}
 
 struct AppendArgs {
     const uint16_t *src;

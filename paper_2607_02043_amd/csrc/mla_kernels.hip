@@ -433,10 +433,15 @@ __device__ __forceinline__ void store_out4(const AttnArgs &a, int row, int head,
 // of splits go out together, and rows cut into many parts spread over
 // more wavefronts, so a row takes one or two rounds.  (One thread loop per head
 // and row before, a block-wide scan of the lengths in front: 18.2 us for 4 rows
-// of 75 parts, now 8.3; 16.5 -> 12.2 us for 128 rows of up to 23 parts; 20.9 ->
-// 12.1 us for 1069 chunk rows and 37 decode rows.  More workgroups per
-// row of few parts cost more in launches than they overlap: 256 rows of
-// 2 to 4 parts take 10.5 us with 4 workgroups a row, 15.6 with 8.)
+// of 75 parts, now 8.3; 16.5 -> 12.2 us for 128 rows of up to 23 parts.  More
+// workgroups per row of few parts cost more in launches than they overlap: 256
+// rows of 2 to 4 parts take 10.5 us with 4 workgroups a row, 15.6 with 8.)
+// Chunk rows of up to 4 parts take one workgroup, four heads a wavefront one
+// after the other: 20.9 -> 9.8 us for 1069 of them and 37 decode rows.  With more
+// parts that chain loses, so they are spread as decode rows are: 8 rows of 65
+// parts 62.0 us before, 71.9 with the chain, 7.8 spread; 64 rows of 9 parts 12.6,
+// 15.1 and 6.9; 2048 rows of 7 parts 136.9, 119.7 and 94.3.  Only rows that have
+// partials get workgroups (the chain's launch had one per item and block row).
 struct SplitRef {
     const float *o, *ml;
 };
@@ -525,7 +530,7 @@ __device__ void merge_heads(const AttnArgs &a, int row, int hh0, int nsplit, Slo
     store_merged(a, row, hh, lane, o, M, den);
 }
 
-// A whole row, four heads per wavefront.
+// A whole row of few parts, four heads per wavefront.
 template <typename Slot>
 __device__ void merge_row(const AttnArgs &a, int row, int nsplit, Slot slot) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -981,10 +986,89 @@ __device__ void decode_merge(const AttnArgs &a, int k, int part, float *s_o, flo
         return SplitRef{a.ws_dec_o + sl * kHeads * kDv, a.ws_dec_ml + sl * kHeads * 2};
     };
     const int n = w1 - w0 + 1;
-    if constexpr (MANY)
+    if (MANY && a.merge_many)
         merge_heads<8, 4>(a, row, part, n, slot, s_o, s_ml);
     else
         merge_heads<4, 1>(a, row, 4 * part, n, slot, s_o, s_ml);
+}
+
+// The k-th row of the chunk requests whose keys are cut into ranges (requests
+// in item order): its request and the number of items of the requests before.
+struct ChunkRow {
+    Located lc;  // local: the row's index in its request
+    int items;
+};
+template <int Q>
+__device__ __forceinline__ bool find_chunk_row_in(const AttnArgs &a, int k, ChunkRow &cr) {
+    const int lane = threadIdx.x & 63;
+    const auto req = [&](int i) { return a.chunk_rev != 0 ? a.num_reqs - 1 - i : i; };
+    const ChunkCount count{a.ks_chunk, a.route};
+    int rows = 0, items = 0;  // of the requests before this step's
+    LenRow cur[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) cur[q] = load_lens(a.cu_q, a.prefix, req(64 * q + lane), a.num_reqs);
+    for (int base = 0; base < a.num_reqs; base += 64 * Q) {
+        LenRow nxt[Q];
+        if constexpr (Q > 1) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q) nxt[q] = load_lens(a.cu_q, a.prefix, req(base + 64 * (Q + q) + lane), a.num_reqs);
+        }
+        int ni[Q], nr[Q], inc_i[Q], inc_r[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int c = cur[q].next - cur[q].row0;
+            ni[q] = base + 64 * q + lane < a.num_reqs ? count(cur[q].p, c) : 0;
+            nr[q] = ni[q] > ceil_div(c, kChunkBlockTokens) ? c : 0;  // more items than blocks: cut into ranges
+            inc_i[q] = wave_scan(ni[q]);
+            inc_r[q] = wave_scan(nr[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int end = rows + inc_r[q], first = end - nr[q];
+            const uint64_t hit = __builtin_amdgcn_ballot_w64(nr[q] > 0 && k >= first && k < end);
+            if (hit != 0) {
+                const int l = __builtin_ctzll(hit);
+                cr.lc = Located{req(base + 64 * q + l), k - __builtin_amdgcn_readlane(first, l),
+                                __builtin_amdgcn_readlane(cur[q].p, l), __builtin_amdgcn_readlane(cur[q].row0, l),
+                                __builtin_amdgcn_readlane(cur[q].next - cur[q].row0, l)};
+                cr.items = items + __builtin_amdgcn_readlane(inc_i[q] - ni[q], l);
+                return true;
+            }
+            rows = __builtin_amdgcn_readlane(end, 63);
+            items += __builtin_amdgcn_readlane(inc_i[q], 63);
+        }
+        if constexpr (Q == 1) break;  // at most 64 requests
+#pragma unroll
+        for (int q = 0; q < Q; ++q) cur[q] = nxt[q];
+    }
+    return false;
+}
+
+// Workgroup `part` of row k of the split chunk requests.
+template <bool MANY>
+__device__ void chunk_merge(const AttnArgs &a, int k, int part, float *s_o, float *s_ml) {
+    ChunkRow cr;
+    if (!(a.num_reqs <= 64 ? find_chunk_row_in<1>(a, k, cr) : find_chunk_row_in<kLookupQ>(a, k, cr))) return;
+    end_lookup();
+    // the row's block: its item of key range 0, and ranges 1, 2, .. behind it
+    Located lc = cr.lc;
+    const int nks = ceil_div(lc.p + lc.c, a.ks_chunk), j = lc.local % kChunkBlockTokens;
+    lc.local = (ceil_div(lc.c, kChunkBlockTokens) - 1 - lc.local / kChunkBlockTokens) * nks;
+    const ChunkItem it = decode_chunk_item(a, lc);
+    const int item = cr.items + lc.local;
+    if (it.nks_eff <= 1 || item + it.nks_eff > a.n_chunk_items) return;
+    if (it.p < 0 || it.row0 < 0 || it.row0 + it.i1 > a.num_rows) return;
+    const auto slot = [&](int ks) {
+        const size_t prow = (size_t)(item + ks) * kChunkBlockTokens + j;
+        return SplitRef{a.ws_chunk_o + prow * kPartialFloats, a.ws_chunk_ml + prow * kPartialStats};
+    };
+    const int row = it.row0 + it.i0 + j;
+    if (MANY && a.chunk_merge_wgs == kHeads)
+        merge_heads<8, 4>(a, row, part, it.nks_eff, slot, s_o, s_ml);
+    else if (a.chunk_merge_wgs == kHeads / 4)
+        merge_heads<4, 1>(a, row, 4 * part, it.nks_eff, slot, s_o, s_ml);
+    else
+        merge_row(a, row, it.nks_eff, slot);
 }
 
 // ------------------------------------------------------------- chunk path
@@ -1502,30 +1586,19 @@ __host__ __device__ __forceinline__ int merge_dec_wgs(const AttnArgs &a) {
 }
 
 // Split merges, after the attention kernel (the kernel boundary makes every
-// partial visible): first merge_wgs workgroups per split decode row, then one per (chunk item, block row).
+// partial visible): first merge_wgs workgroups per split decode row, then
+// chunk_merge_wgs per row of the split chunk requests.  MANY: some rows take a
+// workgroup per head.
 template <bool MANY>
 __global__ __launch_bounds__(kThreads, MANY ? 4 : 5) void combine_kernel(AttnArgs a) {
     __shared__ __attribute__((aligned(16))) float s_o[4 * kDv];
     __shared__ float s_ml[8];
     const int b = blockIdx.x;
     const int n_dec = merge_dec_wgs(a);
-    if (b < n_dec) {
+    if (b < n_dec)
         decode_merge<MANY>(a, b / merge_wgs(a), b % merge_wgs(a), s_o, s_ml);
-        return;
-    }
-    // one workgroup per (chunk item, row of its block): the item with key split
-    // 0 merges that row over the block's splits
-    const int item = (b - n_dec) / kChunkBlockTokens, j = (b - n_dec) % kChunkBlockTokens;
-    Located lc;
-    if (!locate_item(item, a.num_reqs, ReqLens{a.cu_q, a.prefix, a.chunk_rev != 0}, ChunkCount{a.ks_chunk, a.route}, lc)) return;
-    const ChunkItem it = decode_chunk_item(a, lc);
-    if (it.ks != 0 || it.nks_eff <= 1 || a.ws_chunk_o == nullptr || j >= it.i1 - it.i0) return;
-    if (it.p < 0 || it.row0 < 0 || it.row0 + it.i1 > a.num_rows) return;
-    // split ks of this block is item + ks
-    merge_row(a, it.row0 + it.i0 + j, it.nks_eff, [&](int ks) {
-        const size_t prow = (size_t)(item + ks) * kChunkBlockTokens + j;
-        return SplitRef{a.ws_chunk_o + prow * kPartialFloats, a.ws_chunk_ml + prow * kPartialStats};
-    });
+    else
+        chunk_merge<MANY>(a, (b - n_dec) / a.chunk_merge_wgs, (b - n_dec) % a.chunk_merge_wgs, s_o, s_ml);
 }
 
 // ----------------------------------------------------------------- append
@@ -1641,13 +1714,13 @@ hipError_t launch_attention(const AttnArgs &a, hipStream_t s) {
 }
 
 hipError_t launch_combine(const AttnArgs &a, hipStream_t s) {
-    // only the kinds that left partials get workgroups
+    // only the rows that left partials get workgroups
     const long long grid_ll =
-        (long long)merge_dec_wgs(a) + (a.ws_chunk_o != nullptr ? (long long)a.n_chunk_items * kChunkBlockTokens : 0);
+        (long long)merge_dec_wgs(a) + (a.ws_chunk_o != nullptr ? (long long)a.n_split_chunk_rows * a.chunk_merge_wgs : 0);
     if (grid_ll > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const int grid = (int)grid_ll;
     if (grid == 0) return hipSuccess;
-    if (a.merge_many)
+    if (a.merge_many || a.chunk_merge_wgs == kHeads)
         hipLaunchKernelGGL(combine_kernel<true>, dim3(grid), dim3(kThreads), 0, s, a);
     else
         hipLaunchKernelGGL(combine_kernel<false>, dim3(grid), dim3(kThreads), 0, s, a);

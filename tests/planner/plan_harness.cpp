@@ -8,6 +8,7 @@
 // Output, one line per batch:
 //   ok ks n_chunk_items n_dec_items unit_tiles dec_total grid merge_many chunk_split split_rows bytes
 //      off_chunk_o off_chunk_ml off_dec_o off_dec_ml plan_us warm est_us dec_first_wgs
+//      split_chunk_rows chunk_merge_wgs
 // or "err <status> <message>".
 // A line "ws <bytes> page_size R q_0 p_0 ..." instead calls the real
 // mixed_step_attn entry point with fake device pointers and a workspace of
@@ -185,7 +186,8 @@ int main() {
                   << pl.dec_unit_tiles << " " << pl.dec_total_tiles << " " << pl.grid << " " << (int)pl.merge_many << " "
                   << (int)pl.chunk_split << " " << pl.n_split_rows << " " << pl.bytes << " " << pl.off_chunk_o << " "
                   << pl.off_chunk_ml << " " << pl.off_dec_o << " " << pl.off_dec_ml << " " << us << " "
-                  << (int)pl.warm << " " << pl.est_us << " " << pl.dec_first_wgs << "\n";
+                  << (int)pl.warm << " " << pl.est_us << " " << pl.dec_first_wgs << " " << pl.n_split_chunk_rows << " "
+                  << pl.chunk_merge_wgs << "\n";
     }
     return 0;
 }

@@ -49,6 +49,31 @@ def test_chunk_rows_of_one_to_five_parts(chunk):
     assert_close(g.out_np(), out_ref, g.lse_np(), lse_ref, what=wl.name)
 
 
+@pytest.mark.parametrize("parts", [2, 4, 5, 9, 16, 17, 33, 70])
+@pytest.mark.parametrize("last_longest", [False, True])
+def test_chunk_row_of_many_parts(parts, last_longest):
+    """64-key ranges: the rows of one chunk are cut into up to `parts` parts,
+    beside a chunk of one range, one of two or three, and decode rows, whole or cut
+    into one-tile units; the longest chunk first or last (the items of the last
+    request then come first)."""
+    log(f"[gpu] chunk rows of up to {parts} parts, last_longest={last_longest}")
+    reqs = [(64 * parts - 11, 11), (30, 1), (10, 17), (100, 9), (700, 1)]
+    if last_longest:
+        reqs.reverse()
+    wl = W.custom([p for p, _ in reqs], [c for _, c in reqs], page_size=16, seed=parts, name=f"chunk rows of {parts} parts")
+    li = wl.layer(0)
+    mla.debug_set(mla.MLA_DEBUG_CHUNK_KEYS, 64)
+    mla.debug_set(mla.MLA_DEBUG_DEC_UNIT, 1 if parts % 2 else 64)
+    try:
+        g = run_layer(wl.batch, li, fused=True)
+    finally:
+        mla.debug_set(mla.MLA_DEBUG_CHUNK_KEYS, 0)
+        mla.debug_set(mla.MLA_DEBUG_DEC_UNIT, 0)
+    pool_ref, out_ref, lse_ref = oracle.step(wl.batch, li, W.SOFTMAX_SCALE)
+    assert np.array_equal(g.pool_np(), pool_ref)
+    assert_close(g.out_np(), out_ref, g.lse_np(), lse_ref, what=wl.name)
+
+
 @pytest.mark.parametrize("reqs", [1, 63, 64, 65, 130])
 def test_append_of_many_requests(reqs):
     rng = np.random.default_rng(reqs)

@@ -57,6 +57,7 @@ def plan(exe, batches, route=None, chunk_keys=None, dec_unit=None, dec_first=Non
                 "split_rows", "bytes", "off_co", "off_cml", "off_do", "off_dml"]
         d = {k: int(v) for k, v in zip(keys, f[1:15])}
         d["us"], d["est"], d["first"] = float(f[15]), float(f[17]), int(f[18])
+        d["split_chunk_rows"], d["chunk_wgs"] = int(f[19]), int(f[20])
         res.append(d)
     return res
 
@@ -111,6 +112,11 @@ def check_plan(batch, d, route=None):
     # chunk items: ceil(c / 8) blocks x ceil((p + c) / ks) key splits per request
     assert d["n_chunk_items"] == sum(-(-c // BLOCK_TOKENS) * -(-(pp + c) // ks) for pp, c in chunks)
     assert d["chunk_split"] == int(any(pp + c > ks for pp, c in chunks))
+    # the merge is launched for the rows of the requests cut into ranges, with
+    # one workgroup a row, or four or sixteen where some have many parts
+    assert d["split_chunk_rows"] == sum(c for pp, c in chunks if pp + c > ks)
+    parts = max((-(-(pp + c) // ks) for pp, c in chunks), default=1)
+    assert d["chunk_wgs"] == (16 if parts > 16 else 4 if parts > 4 else 1)
     if chunks:
         assert ks % 64 == 0 and ks >= 64
         assert ks <= max(64, (PAGE_WINDOW - 1) * P // 64 * 64)  # an item's keys fit the page window
@@ -300,6 +306,7 @@ def _serving_plans(harness, batches):
                 "split_rows", "bytes", "off_co", "off_cml", "off_do", "off_dml"]
         d = {k: int(v) for k, v in zip(keys, f[1:15])}
         d["us"], d["warm"], d["first"] = float(f[15]), int(f[16]), int(f[18])
+        d["split_chunk_rows"], d["chunk_wgs"] = int(f[19]), int(f[20])
         res.append(d)
     assert len(res) == len(batches)
     return res
